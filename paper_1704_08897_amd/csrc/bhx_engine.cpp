@@ -210,13 +210,13 @@ int engine_rows(const bhx_engine* E) {
 // captured graphs survive changes of the active set) and LDS from the
 // largest transform among the requests.
 Grids engine_grids(bhx_engine* E, const std::vector<Req*>& reqs) {
-  Grids g;
+  Grids g{};
   const int cu = E->hd->num_cu;
   g.s = cu * 8;
   g.r = cu * 2;
   g.c = cu * 2;
   const int csize = E->R.precision == 0 ? 16 : 8;
-  int buf_r = 0, buf_c = 0;
+  int buf_r = 0, lds_c = 0;
   int any_dense = 0;
   g.count = (int)reqs.size();
   for (Req* q : reqs) {
@@ -226,11 +226,10 @@ Grids engine_grids(bhx_engine* E, const std::vector<Req*>& reqs) {
       continue;
     }
     const AxisPlan& PX = E->hd->plans.plan(q->inst.planx);
-    const AxisPlan& PY = E->hd->plans.plan(q->inst.plany);
-    plan_family(PX, q->inst.G / 2, &g.shape_r);  // plan-table kernel families
-    plan_family(PY, q->inst.Gc / 2, &g.shape_c);
+    plan_family(PX, q->inst.G / 2, &g.shape_r);  // plan-table kernel family
     buf_r = std::max(buf_r, (q->inst.G / 2) * row_slots(PX.m));
-    buf_c = std::max(buf_c, (q->inst.Gc / 2) * row_slots(PY.m));
+    lds_c = std::max(lds_c, col_lds(q->inst.ny, q->inst.Gc, E->R.precision));
+    g.lng = std::max(g.lng, col_class(q->inst.ny, q->inst.Gc));
   }
   // the engine runs the plan-table kernels, which read their tables from
   // global memory: LDS for the packed rows alone, rounded up to 4 KiB steps
@@ -239,8 +238,8 @@ Grids engine_grids(bhx_engine* E, const std::vector<Req*>& reqs) {
   auto up = [](int b) { return (b + 4095) / 4096 * 4096; };
   g.tw_r = buf_r;
   g.lds_r = std::min(kLdsDynMax, up(buf_r * csize));
-  g.tw_c = buf_c;
-  g.lds_c = std::min(kLdsDynMax, up(buf_c * csize));
+  g.tw_c = 0;
+  g.lds_c = std::min(kLdsDynMax, up(lds_c));
   // the FFT family launches every iteration (with no request on it it
   // returns at once); the dense passes, sized for the longest dense axis,
   // only while a dense request is active.  The captured graphs depend on the
@@ -278,6 +277,8 @@ int setup_new(bhx_engine* E, std::vector<Req*>& news, hipStream_t st) {
     I.nx = S.nx; I.ny = S.ny; I.nz = 1; I.nrows = S.ny;
     I.bcx = S.bcx; I.bcy = S.bcy;
     I.planx = px; I.plany = py;
+    I.lamx = hd->plans.plan(px).off_lam;
+    I.lamy = hd->plans.plan(py).off_lam;
     I.G = L.G; I.Gc = L.Gc; I.tiles_x = L.tiles_x; I.tiles_y = L.tiles_y; I.tiles_z = 1;
     for (int p = 0; p < kNumPass; ++p) I.n_items[p] = L.n_items[p];
     I.maxit = E->R.maxit_user > 0 ? E->R.maxit_user : 50 * std::max(S.nx, S.ny);

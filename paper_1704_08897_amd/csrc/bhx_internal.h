@@ -33,7 +33,13 @@ constexpr int kLdsBytes = 80 * 1024;   // LDS for the packed rows of one transfo
 constexpr int kLdsMax = 160 * 1024;    // LDS of a CU (gfx950)
 constexpr int kLdsDynMax = 152 * 1024; // dynamic LDS cap of a transform launch
 constexpr int kMaxPairs = 8;           // (k, n-k) pairs held in registers per thread
-constexpr int kMaxGc = 16;             // columns per column-pass item (2 x rows cap)
+constexpr int kMaxGc = 16;             // y pencils per item (three dimensions)
+constexpr int kColThreads = 512;       // threads of the column solve
+constexpr int kColWaves = kColThreads / 64;
+constexpr int kColWide = 4 * kColWaves;   // columns of its wide items (16 lanes a column),
+                                       // else kColWaves (64 lanes)
+constexpr int kColWideMax = 512;       // longest axis of wide items
+constexpr int kColWideMin = 4096;      // columns one instance needs for wide items
 constexpr int kTargetItems = 512;      // row/column items one instance should supply
 // Partial-sum arrays longer than this (tiles + 3 x row groups) are reduced
 // once per pass by a one-block launch instead of in every consumer block.
@@ -80,6 +86,26 @@ __host__ __device__ inline int table_slots(int n, int m, int bc, bool lam) {
   const int np = plan_pairs(n, bc);
   return stage_twiddles(31 - __builtin_clz(m)) + (bc == 0 ? np : 0) + (lam ? (np + 1) / 2 : 0);
 }
+// Column solve: rows a lane holds of a column of n nodes in items of W columns
+// (a power of two), and the columns' stride in LDS: whole segments, one slot
+// more after each to spread the lanes' loads over the banks, the rest for the
+// staging.
+__host__ __device__ inline int col_rows(int n, int W) {
+  const int lanes = W == kColWide ? 16 : 64;
+  int r = 1;
+  while (r * lanes < n) r <<= 1;
+  return r;
+}
+// Kernel class of the column solve for such columns: 0 at most 8 rows a lane,
+// 1 at most 32, 2 more (FP32 only).
+inline int col_class(int n, int W) {
+  const int r = col_rows(n, W);
+  return r <= 8 ? 0 : r <= 32 ? 1 : 2;
+}
+__host__ __device__ inline int col_stride(int n, int lc, int W) {
+  const int s = (n + lc - 1) / lc * (lc > 1 ? lc + 1 : 1);
+  return W == kColWide ? s | 1 : (s + 27) / 32 * 32 + 4;
+}
 // Ghost-node rule of one axis: global index g in [-2, n+1] -> stored index,
 // with sign s (Dirichlet odd reflection of Algorithm 1: g[-1] = 0,
 // g[-2] = -f[0]); Neumann half-sample even reflection; periodic wrap.
@@ -93,8 +119,9 @@ __device__ __forceinline__ int map_axis(int g, int n, int bc, double& s) {
   return g < 0 ? 0 : n - 1;
 }
 
-// Work lists: stencil tiles, row groups, column groups, z-pencil groups, and
-// the row and column groups of instances whose preconditioner runs as dense
+// Work lists: stencil tiles, row groups, column groups (two dimensions: of the
+// column solve along y; three: y pencils), groups of the column solve along z,
+// and the row and column groups of instances whose preconditioner runs as dense
 // matrix products (kPassRD, kPassCD; those instances are absent from the
 // kPassR and kPassC lists).
 enum Pass { kPassS = 0, kPassR = 1, kPassC = 2, kPassZ = 3, kPassRD = 4, kPassCD = 5,
@@ -105,12 +132,9 @@ enum Pass { kPassS = 0, kPassR = 1, kPassC = 2, kPassZ = 3, kPassRD = 4, kPassCD
 constexpr int kDenseG = 16;
 constexpr int kDenseMax = 512;
 
-// Kinds of column-transform launch.  Two dimensions: one launch transforms
-// along y, scales by 1/(lambda_x + lambda_y)^2 and transforms back.  Three
-// dimensions: forward along y, then along z with the scale by
-// 1/(lambda_x + lambda_y + lambda_z)^2 and the inverse along z, then the
-// inverse along y.
-enum ColKind { kCol2D = 0, kColYFwd = 1, kColZ = 2, kColYInv = 3 };
+// Kinds of the y transform of three dimensions, before and after the column
+// solve along z.
+enum ColKind { kColYFwd = 0, kColYInv = 1 };
 
 // Stencil kernel modes.
 enum SMode {
@@ -187,9 +211,11 @@ struct Inst {
   int nrows;            // x rows: ny * nz
   int bcx, bcy, bcz;
   int planx, plany, planz;   // AxisPlan indices (planz unused in two dimensions)
+  int lamx, lamy;       // offsets of the x and y eigenvalues in the real table
   int G;                // rows per item in the row passes (even)
-  int Gc;               // columns per item in the column pass (even)
-  int Gz;               // z pencils per item in the z pass (even; three dimensions)
+  int Gc;               // columns per item of the column solve (two dimensions) or y
+                        //    pencils per item (three, even); kDenseG if dense
+  int Gz;               // columns per item of the column solve (three dimensions)
   int tiles_x, tiles_y, tiles_z; // stencil tiles
   int n_items[kNumPass];
   int maxit;
@@ -206,7 +232,8 @@ struct Inst {
   BHX_GLOBAL double* p[2];    // search direction, double-buffered by iteration parity
   BHX_GLOBAL double* q;
   BHX_GLOBAL double* z;
-  BHX_GLOBAL void* t;         // transform buffer, [nx][nz][ny] (y fastest), double or float
+  BHX_GLOBAL void* t;         // transform buffer, laid out as the field ([nz][ny][nx], x
+                              // fastest); [nx][ny] if dense; double or float
   BHX_GLOBAL double* part;    // partial sums, see PartLayout
   BHX_GLOBAL Ctl* ctl;
 };
@@ -277,7 +304,7 @@ hipError_t launch_resid(const Batch* B, int dim, int grid, hipStream_t st);
 // instance runs instead.  shape_key() gives it for one instance's axis of
 // pass family `pass` (ShapePass), or 0 when that shape is not instantiated; a
 // batch uses it when every instance has that axis plan and grouping.
-enum ShapePass { kShapeRow = 0, kShapeCol2D = 1, kShapeColY = 2, kShapeColZ = 3 };
+enum ShapePass { kShapeRow = 0, kShapeY = 1 };
 // Plan-table kernel families (`shape` values below 2^8, which no compile-time
 // shape takes): kShapeNarrowKey (0) has only the one-stage FFT passes, which
 // keeps its register use low; kShapeWideKey also has the 16-point passes,
@@ -293,18 +320,17 @@ constexpr int kFftWideLaunch = 4096;
 // have G >= 2 in bits 8 and up.
 inline bool plan_table_shape(int shape) { return shape < 256; }
 int shape_key(int pass, int prec, int n, int m, int logm, int bluestein, int bc, int group);
-// `stream_t` != 0: the row-forward pass writes t with non-temporal stores.
-// Its transposed store writes G-element pieces of many lines.  While the
-// launch's whole t is small the pass is latency-bound, and streaming those
-// pieces past the L2 shortens the write-back at the kernel's end; on a large
-// t the unmerged pieces cost HBM bandwidth instead.  The runtime sets it when
-// the launch's t arrays total at most kStreamTMax bytes.
-hipError_t launch_rowfwd(const Batch* B, int prec, int shape, int update, int stream_t, int grid,
-                         int lds, int twoff, int lpar, hipStream_t st, hipEvent_t e0 = nullptr,
+hipError_t launch_rowfwd(const Batch* B, int prec, int shape, int update, int grid, int lds,
+                         int twoff, int lpar, hipStream_t st, hipEvent_t e0 = nullptr,
                          hipEvent_t e1 = nullptr);
-hipError_t launch_col(const Batch* B, int prec, int shape, int kind, int count_iter, int grid,
-                      int lds, int twoff, hipStream_t st, hipEvent_t e0 = nullptr,
-                      hipEvent_t e1 = nullptr);
+// Column solve along the last axis: `pass` kPassC (two dimensions) or kPassZ.
+// `lng`: the largest col_class of the launch.
+hipError_t launch_colsolve(const Batch* B, int prec, int pass, int lng, int count_iter, int grid,
+                           int lds, hipStream_t st, hipEvent_t e0 = nullptr,
+                           hipEvent_t e1 = nullptr);
+// y transform of three dimensions (`kind`: ColKind).
+hipError_t launch_ypass(const Batch* B, int prec, int shape, int kind, int grid, int lds,
+                        int twoff, hipStream_t st);
 hipError_t launch_rowinv(const Batch* B, int prec, int shape, int grid, int lds, int twoff,
                          int lpar, hipStream_t st, hipEvent_t e0 = nullptr,
                          hipEvent_t e1 = nullptr);

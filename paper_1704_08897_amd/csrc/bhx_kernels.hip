@@ -4,16 +4,18 @@
 // unfinished instance of a batch:
 //   S  (k_stencil, mode iter): p = z + beta p; q = A p at unknown nodes; p.q
 //   R  (k_rowfwd, update):     alpha = r.z / p.q; x += alpha p; r -= alpha q;
-//                              ||r||^2; forward transform of r along x,
-//                              written transposed ([nx][ny], y fastest)
-//   C  (k_col):                forward transform along y, divide by
-//                              (lambda_x + lambda_y)^2, inverse along y
+//                              ||r||^2; forward transform of r along x -> t
+//   C  (k_colsolve):           (lambda_x + T_y)^-2 along y, column by column,
+//                              by first-order recursions (three dimensions:
+//                              k_ypass forward, the solve along z, k_ypass
+//                              inverse)
 //   RI (k_rowinv):             inverse transform along x, restrict to the
 //                              unknown nodes -> z; r.z (and r.z_old)
 // The method is Sec. 2.2 and Algorithm 1 of the paper: the 13-point stencil
 // of eq. (12) evaluated on demand as the 5-point Laplacian applied twice over
 // two ghost layers, and the fast Poisson preconditioner (embed, transform,
-// scale by the inverse squared eigenvalues, transform back, restrict).
+// scale by the inverse squared eigenvalues, transform back, restrict), with
+// the last axis solved directly instead of transformed.
 //
 // Transforms: Neumann axes use the orthonormal DCT-II (inverse DCT-III)
 // through a complex FFT of the same length (Makhoul's even/odd reordering);
@@ -50,6 +52,10 @@ template <> struct V2<float> { using T = float2; };
 
 template <typename C> __device__ __forceinline__ C mk(decltype(C::x) a, decltype(C::x) b) {
   C c; c.x = a; c.y = b; return c;
+}
+// from two doubles, rounded to C's precision
+template <typename C> __device__ __forceinline__ C mk2(double a, double b) {
+  return mk<C>((decltype(C::x))a, (decltype(C::x))b);
 }
 template <typename C> __device__ __forceinline__ C cadd(C a, C b) { return mk<C>(a.x + b.x, a.y + b.y); }
 template <typename C> __device__ __forceinline__ C csub(C a, C b) { return mk<C>(a.x - b.x, a.y - b.y); }
@@ -477,8 +483,8 @@ struct XPlan {
   }
   // FFT bin holding spectral index k (DST-I: bin k+1 of the odd extension)
   __device__ __forceinline__ int bin(int k) const { return bc == kDirichlet ? k + 1 : k; }
-  // Forward-transform input: sample i of half h (one of two real rows) of a
-  // packed row.  DCT-II: Makhoul order; Hartley: in order; DST-I: +x at
+  // Forward-transform input without the chirp: sample i of half h (one of two
+  // real rows) of a packed row.  DCT-II: Makhoul order; Hartley: in order; DST-I: +x at
   // i+1 and -x at nf-1-i (odd extension), see zero_ends().
   __device__ __forceinline__ void put(C* row, int i, int h, R v) const {
     if (bc == kDirichlet) {
@@ -488,19 +494,32 @@ struct XPlan {
       ((R*)(row + pos(fwd_index(i, n, bc))))[h] = v;
     }
   }
+  // Logical input q of a row, Bluestein's chirp applied on the way in.
+  __device__ __forceinline__ void place(C* row, int q, C v) const {
+    row[pos(q)] = blue ? cmul(v, chirp[q]) : v;
+  }
+  // Both halves of sample i at once (dft_core with the chirp applied).
+  __device__ __forceinline__ void put_both(C* row, int i, C v) const {
+    if (bc == kDirichlet) {
+      place(row, i + 1, v);
+      place(row, nf - 1 - i, mk<C>(-v.x, -v.y));
+    } else {
+      place(row, fwd_index(i, n, bc), v);
+    }
+  }
   // Inputs of the second transform of a pass (values a at k, b at partner
-  // kk), placed like put() but for both halves at once.
+  // kk; the chirp applied).
   __device__ __forceinline__ void put_pair(C* row, int k, int kk, C a, C b) const {
     if (bc == kDirichlet) {
-      row[pos(k + 1)] = a;
-      row[pos(nf - 1 - k)] = mk<C>(-a.x, -a.y);
+      place(row, k + 1, a);
+      place(row, nf - 1 - k, mk<C>(-a.x, -a.y));
       if (kk != k) {
-        row[pos(kk + 1)] = b;
-        row[pos(nf - 1 - kk)] = mk<C>(-b.x, -b.y);
+        place(row, kk + 1, b);
+        place(row, nf - 1 - kk, mk<C>(-b.x, -b.y));
       }
     } else {
-      row[pos(k)] = a;
-      if (kk != k) row[pos(kk)] = b;
+      place(row, k, a);
+      if (kk != k) place(row, kk, b);
     }
   }
   // DST-I: the odd extension is zero at 0 and n+1 (no other rule writes them);
@@ -513,9 +532,10 @@ struct XPlan {
       if (!cz) buf[r * st + pos(n + 1)] = mk<C>(0, 0);
     }
   }
-  // Chirp-z DST-I: sample i of the row's one real line at point i + 1.
+  // Chirp-z DST-I: sample i of the row's one real line at point i + 1 (the
+  // chirp applied).
   __device__ __forceinline__ void put_cz(C* row, int i, R v) const {
-    row[pos(i + 1)] = mk<C>(v, (R)0);
+    place(row, i + 1, mk<C>(v, (R)0));
   }
   // Chirp-z DST-I: orthonormal coefficient k of the row's line.  The row
   // holds sum_{j=1..n} x_j W^(jk), W = exp(-2 pi i / (2(n+1))), whose
@@ -607,12 +627,13 @@ template <typename C> __device__ __forceinline__ void bfly2(C& a0, C& a1) {
   a1 = csub(u, v);
 }
 
-enum { kFftChirp = 1, kFftDit = 2, kFftBhat = 4, kFftDif = 8 };
+enum { kFftChirp = 1, kFftDit = 2, kFftBhat = 4, kFftDif = 8, kFftZero = 16 };
 
 // One pass of RAD points (4, 8 or 16) and span 2^lh over `rows` rows of
 // length 2^logm (stride st, pad shift sh).  `fl` selects, in this order: the
-// chirp on the inputs (Bluestein; inputs at logical index >= nf are zero),
-// the forward stages, the product with the kernel spectrum bhat, the inverse
+// chirp on the inputs (kFftChirp; inputs at logical index >= nf are zero) or,
+// where it was applied as they were placed, the zeros alone (kFftZero); the
+// forward stages, the product with the kernel spectrum bhat, the inverse
 // stages.  Stage twiddles: the table of span h starts at (h - h0) / 3.
 template <typename R, int RAD, bool TG>
 __device__ __forceinline__ void fft_pass(typename V2<R>::T* buf, int rows, int st, int logm,
@@ -641,12 +662,12 @@ __device__ __forceinline__ void fft_pass(typename V2<R>::T* buf, int rows, int s
     C v[RAD];
 #pragma unroll
     for (int j = 0; j < RAD; ++j) v[j] = a[rpos(base + (j << lh), sh)];
-    if (fl & kFftChirp) {
+    if (fl & (kFftChirp | kFftZero)) {
 #pragma unroll
       for (int j = 0; j < RAD; ++j) {
         const int q = bitrev(base + (j << lh), logm);
-        const C c = chirp[min(q, nf - 1)];
-        v[j] = q < nf ? cmul(v[j], c) : mk<C>(0, 0);
+        if (fl & kFftChirp) v[j] = cmul(v[j], chirp[min(q, nf - 1)]);
+        v[j] = q < nf ? v[j] : mk<C>(0, 0);
       }
     }
     if (fl & kFftDit) {
@@ -706,9 +727,10 @@ __device__ __forceinline__ void fft_fixed(typename V2<R>::T* buf, int rows, int 
 
 // After inputs are placed at pos(k) (k < nf): the forward DFT of length nf of
 // every row.  Power-of-two nf: the FFT passes, natural-order output.
-// Otherwise Bluestein: chirp (zero past nf), FFT, product with the kernel
-// spectrum, inverse FFT (bit-reversed output; out() applies the final chirp).
-template <bool W, typename R, int SP>
+// Otherwise Bluestein: chirp (applied already if CHIRPED; zero past nf), FFT,
+// product with the kernel spectrum, inverse FFT (bit-reversed output; out()
+// applies the final chirp).
+template <bool W, bool CHIRPED, typename R, int SP>
 __device__ void dft_core(const XPlan<R, SP>& X, typename V2<R>::T* buf, int rows) {
   if constexpr (SP != 0) {
     constexpr int L = (SP >> 2) & 63;
@@ -731,7 +753,7 @@ __device__ void dft_core(const XPlan<R, SP>& X, typename V2<R>::T* buf, int rows
     for (int s = 0; s < nstep; ++s) {
       const int p = s < np ? s : 2 * np - 2 - s;
       int fl = s < np ? kFftDit : kFftDif;
-      if (blue && s == 0) fl |= kFftChirp;
+      if (blue && s == 0) fl |= CHIRPED ? kFftZero : kFftChirp;
       if (blue && s == np - 1) fl |= kFftBhat | kFftDif;
       const int rad = fft_pass_rad(logm, p, wide), lh = fft_pass_lspan(logm, p, wide);
       // twiddles from the global table (no LDS tables in these instances)
@@ -1300,28 +1322,24 @@ __global__ void __launch_bounds__(kThreads) k_resid(const Batch* __restrict__ Bp
 
 // ---------------------------------------------------------------------------
 // Row pass, forward: optional CG update, then forward transform of r along x
-// for G rows, written transposed to t[k * nrows + j].  Rows are the x lines:
-// j = y in two dimensions, j = z * ny + y in three (nrows = ny * nz).
+// for G rows, written to t[j * nx + k].  Rows are the x lines: j = y in two
+// dimensions, j = z * ny + y in three (nrows = ny * nz).
 // ---------------------------------------------------------------------------
 
-// `mode`: bits 0-1 the update (0 none, 1 PCG update then transform, 2 plain
-// CG update only), bit 2 set: store t with non-temporal stores.  `lpar`:
-// buffer parity of the iteration (as in k_stencil): p_new = p[lpar ^ 1],
-// current r.z partials rz(lpar).  SP: compile-time shape of the x axis and
-// row group (see XPlan), 0 for any shape.
+// `update`: 0 none, 1 PCG update then transform, 2 plain CG update only.
+// `lpar`: buffer parity of the iteration (as in k_stencil): p_new =
+// p[lpar ^ 1], current r.z partials rz(lpar).  SP: compile-time shape of the
+// x axis and row group (see XPlan), 0 for any shape.
 template <typename R, int SP, int FAM = 0>
-__global__ void __launch_bounds__(kThreads) k_rowfwd(const Batch* __restrict__ Bp, int mode,
+__global__ void __launch_bounds__(kThreads) k_rowfwd(const Batch* __restrict__ Bp, int update,
                                                      int twoff, int lpar) {
   using C = typename V2<R>::T;
   constexpr bool CZ = FAM == kFamCz;
   constexpr bool kWide = FAM != kFamNarrow;
-  const int update = mode & 3;
-  const bool stream_t = (mode & 4) != 0;
   const Batch B = *(BHX_CONST const Batch*)Bp;   // scalar loads, kept in registers
   extern __shared__ __align__(16) unsigned char smem[];
   debug_fill_lds(smem);
   C* buf = (C*)smem;
-  R* stg = (R*)smem;
   C* twl = buf + twoff;
   int staged = -1;
   __shared__ double red[8];
@@ -1334,6 +1352,7 @@ __global__ void __launch_bounds__(kThreads) k_rowfwd(const Batch* __restrict__ B
     // ny: rows of the pass
     const int nx = SP ? sp_nodes(SP) : I.nx, ny = I.nrows, G = SP ? SP >> 8 : I.G,
               j0 = g * G;
+    const int rows = G >> 1;
     const int E = min(G, ny - j0) * nx;          // valid elements of this row group
     const size_t base = (size_t)j0 * nx;
     BHX_GLOBAL const uint8_t* __restrict__ mk = I.mask + base;
@@ -1341,45 +1360,58 @@ __global__ void __launch_bounds__(kThreads) k_rowfwd(const Batch* __restrict__ B
     BHX_GLOBAL double* __restrict__ rb = I.r + base;
     BHX_GLOBAL const double* __restrict__ pb = (lpar ? I.p[0] : I.p[1]) + base;
     BHX_GLOBAL const double* __restrict__ qb = I.q + base;
+    // A thread takes both lines of a packed row at its sample, which then go
+    // to LDS as one complex value: sample i of packed row rr is at elements
+    // o = 2 rr nx + i and o + nx of the group.
+    auto offset = [&](int e) {
+      const int rr = rows == 1 ? 0 : e / nx;
+      return e + rr * nx;
+    };
     // 1. issue together: control fields, the row group's unknown count, the
-    //    partial sums behind alpha and the masks of the first kPre elements
-    //    per thread (rows j0 .. j0+G-1 are contiguous); `done` and the counts
-    //    do not change during the pass
+    //    partial sums behind alpha and the masks of the first kPre samples per
+    //    thread; `done` and the counts do not change during the pass
     BHX_GLOBAL const double* arrs[2] = {I.part + PL.rz(lpar), I.part + PL.pq()};
     const int lens[2] = {I.reduce ? 1 : PL.nR, I.reduce ? 1 : PL.nS};
     const int ns[2] = {update && !I.reduce ? PL.nR : 0, update && !I.reduce ? PL.nS : 0};
     Partials<2> PS;
     sums_issue<2>(arrs, lens, PS);             // unconditional: no branch before the loads
     const double rsc[2] = {ctl->red_rz[lpar], ctl->red_pq};
-    int m0[kPre];
+    constexpr int kPair = kPre / 2;
+    const int S = rows * nx;                   // samples
+    int o0[kPair], ma0[kPair], mb0[kPair];
 #pragma unroll
-    for (int u = 0; u < kPre; ++u) {
+    for (int u = 0; u < kPair; ++u) {
       const int e = threadIdx.x + u * kThreads;
-      m0[u] = mk[min(e, E - 1)] && e < E;
+      o0[u] = offset(min(e, S - 1));
+      ma0[u] = mk[min(o0[u], E - 1)] && e < S && o0[u] < E;
+      mb0[u] = mk[min(o0[u] + nx, E - 1)] && e < S && o0[u] + nx < E;
     }
     const int c_done = ctl->done, k_it = ctl->iter;
     const double rowcnt = I.part[PL.rowcnt() + g];
     if (c_done) continue;
     if (rowcnt == 0.0) {
       // no unknown node in these rows: r = 0 there, so is its transform
-      BHX_GLOBAL R* t = (BHX_GLOBAL R*)I.t;
-      for (int e = threadIdx.x; e < nx * G; e += kThreads) {
-        const int kx = e / G, j = j0 + (e - kx * G);
-        if (j < ny) t[(size_t)kx * ny + j] = (R)0;
-      }
+      BHX_GLOBAL R* t = (BHX_GLOBAL R*)I.t + base;
+      for (int e = threadIdx.x; e < E; e += kThreads) t[e] = (R)0;
       if (update && threadIdx.x == 0) I.part[PL.rr() + g] = 0.0;
       continue;
     }
     // 2. values at unknown nodes (lanes of known nodes read element 0: one
     //    cached line per wave), in flight while tables and scalars settle
-    double rv0[kPre], pv0[kPre], qv0[kPre], xv0[kPre];
+    struct Val { double r, p, q, x; };
+    auto load = [&](int o) {
+      Val w;
+      w.r = rb[o];
+      w.p = update ? pb[o] : 0.0;
+      w.q = update ? qb[o] : 0.0;
+      w.x = update ? Fb[o] : 0.0;
+      return w;
+    };
+    Val wa0[kPair], wb0[kPair];
 #pragma unroll
-    for (int u = 0; u < kPre; ++u) {
-      const int ea = m0[u] ? threadIdx.x + u * kThreads : 0;
-      rv0[u] = rb[ea];
-      pv0[u] = update ? pb[ea] : 0.0;
-      qv0[u] = update ? qb[ea] : 0.0;
-      xv0[u] = update ? Fb[ea] : 0.0;
+    for (int u = 0; u < kPair; ++u) {
+      wa0[u] = load(ma0[u] ? o0[u] : 0);
+      wb0[u] = load(mb0[u] ? o0[u] + nx : 0);
     }
     XPlan<R, SP> X(B, I.planx);
     if constexpr (!CZ) X.cz = 0;   // chirp-z axes run on the CZ instances only
@@ -1390,48 +1422,51 @@ __global__ void __launch_bounds__(kThreads) k_rowfwd(const Batch* __restrict__ B
       sums_finish<2>(arrs, ns, PS, sums, red);
       alpha = I.reduce ? rsc[0] / rsc[1] : sums[0] / sums[1];
     }
-    const int rows = G >> 1;
     const int st = X.stride();
     const bool first = k_it == 0;
     double acc = 0.0;
     // 3. update and place r into the packed rows
-    auto consume = [&](int e, int m, double rv, double pv, double qv, double xv) {
-      if (e >= G * nx) return;
-      double v = m ? rv : 0.0;
+    auto step = [&](int o, int m, const Val& w) {
+      double v = m ? w.r : 0.0;
       if (update && m) {
-        Fb[e] = (first && !I.warm ? 0.0 : xv) + alpha * pv;
-        v -= alpha * qv;
-        rb[e] = v;
+        Fb[o] = (first && !I.warm ? 0.0 : w.x) + alpha * w.p;
+        v -= alpha * w.q;
+        rb[o] = v;
         acc += v * v;
       }
+      return v;
+    };
+    auto consume = [&](int e, int o, int ma, int mb, const Val& wa, const Val& wb) {
+      if (e >= S) return;
+      const double va = step(o, ma, wa);
+      const double vb = step(o + nx, mb, wb);
       if (update != 2) {
-        const int jr = e / nx, i = e - jr * nx;
-        if (!X.cz) X.put(buf + (jr >> 1) * st, i, jr & 1, (R)v);
-        else if (!(jr & 1)) X.put_cz(buf + (jr >> 1) * st, i, (R)v);   // first lines now
+        const int rr = rows == 1 ? 0 : e / nx, i = e - rr * nx;
+        if (!X.cz) X.put_both(buf + rr * st, i, mk2<C>(va, vb));
+        else X.put_cz(buf + rr * st, i, (R)va);              // first lines now
       }
     };
 #pragma unroll
-    for (int u = 0; u < kPre; ++u)
-      consume(threadIdx.x + u * kThreads, m0[u], rv0[u], pv0[u], qv0[u], xv0[u]);
-    for (int e0 = threadIdx.x + kPre * kThreads; e0 < G * nx; e0 += kUnroll * kThreads) {
-      int m[kUnroll];
-      double rv[kUnroll], pv[kUnroll], qv[kUnroll], xv[kUnroll];
+    for (int u = 0; u < kPair; ++u)
+      consume(threadIdx.x + u * kThreads, o0[u], ma0[u], mb0[u], wa0[u], wb0[u]);
+    constexpr int kMore = kUnroll / 2;
+    for (int e0 = threadIdx.x + kPair * kThreads; e0 < S; e0 += kMore * kThreads) {
+      int o[kMore], ma[kMore], mb[kMore];
+      Val wa[kMore], wb[kMore];
 #pragma unroll
-      for (int u = 0; u < kUnroll; ++u) {
+      for (int u = 0; u < kMore; ++u) {
         const int e = e0 + u * kThreads;
-        m[u] = mk[min(e, E - 1)] && e < E;
+        o[u] = offset(min(e, S - 1));
+        ma[u] = mk[min(o[u], E - 1)] && e < S && o[u] < E;
+        mb[u] = mk[min(o[u] + nx, E - 1)] && e < S && o[u] + nx < E;
       }
 #pragma unroll
-      for (int u = 0; u < kUnroll; ++u) {
-        const int ea = m[u] ? e0 + u * kThreads : 0;
-        rv[u] = rb[ea];
-        pv[u] = update ? pb[ea] : 0.0;
-        qv[u] = update ? qb[ea] : 0.0;
-        xv[u] = update ? Fb[ea] : 0.0;
+      for (int u = 0; u < kMore; ++u) {
+        wa[u] = load(ma[u] ? o[u] : 0);
+        wb[u] = load(mb[u] ? o[u] + nx : 0);
       }
 #pragma unroll
-      for (int u = 0; u < kUnroll; ++u)
-        consume(e0 + u * kThreads, m[u], rv[u], pv[u], qv[u], xv[u]);
+      for (int u = 0; u < kMore; ++u) consume(e0 + u * kThreads, o[u], ma[u], mb[u], wa[u], wb[u]);
     }
     if (update != 2) X.zero_ends(buf, rows, st);
     __syncthreads();
@@ -1441,83 +1476,55 @@ __global__ void __launch_bounds__(kThreads) k_rowfwd(const Batch* __restrict__ B
       if (update == 2) continue;       // plain CG: update only
     }
     // 2. FFT
-    dft_core<kWide>(X, buf, rows);
-    // 3. real spectra of the pairs (k, n-k) into registers
+    dft_core<kWide, true>(X, buf, rows);
+    // 3. real spectra of the pairs (k, n-k), stored from registers: the lanes
+    //    of a wave hold neighbouring k, so both runs (ascending k, descending
+    //    n-k) of a row go out in whole lines
     const int np = X.pairs();
-    R va[kMaxPairs][4];
+    BHX_GLOBAL R* t = (BHX_GLOBAL R*)I.t + base;
     if (X.cz) {
       // chirp-z DST-I: the first line of each pair is in its row now; then
       // the second, whose updated r this block wrote to rb above
-#pragma unroll
-      for (int s = 0; s < kMaxPairs; ++s) {
-        const int pidx = threadIdx.x + s * kThreads;
-        if (pidx < rows * np) {
+#pragma unroll 1
+      for (int h = 0; h < 2; ++h) {
+        for (int pidx = threadIdx.x; pidx < rows * np; pidx += kThreads) {
           const int rr = pidx / np, k = pidx - rr * np;
+          const int jr = 2 * rr + h;
+          if (j0 + jr >= ny) continue;
           const C* row = buf + rr * st;
-          va[s][0] = X.coef_cz(row, k);
-          va[s][2] = X.coef_cz(row, X.partner(k));
+          t[(size_t)jr * nx + k] = X.coef_cz(row, k);
+          t[(size_t)jr * nx + X.partner(k)] = X.coef_cz(row, X.partner(k));
         }
-      }
-      __syncthreads();
-      for (int e = threadIdx.x; e < G * nx; e += kThreads) {
-        const int jr = e / nx, i = e - jr * nx;
-        if (jr & 1) X.put_cz(buf + (jr >> 1) * st, i, (e < E && mk[e]) ? (R)rb[e] : (R)0);
-      }
-      X.zero_ends(buf, rows, st);
-      __syncthreads();
-      dft_core<kWide>(X, buf, rows);
-#pragma unroll
-      for (int s = 0; s < kMaxPairs; ++s) {
-        const int pidx = threadIdx.x + s * kThreads;
-        if (pidx < rows * np) {
-          const int rr = pidx / np, k = pidx - rr * np;
-          const C* row = buf + rr * st;
-          va[s][1] = X.coef_cz(row, k);
-          va[s][3] = X.coef_cz(row, X.partner(k));
+        if (h == 1) break;
+        __syncthreads();
+        for (int e = threadIdx.x; e < G * nx; e += kThreads) {
+          const int jr = e / nx, i = e - jr * nx;
+          if (jr & 1) X.put_cz(buf + (jr >> 1) * st, i, (e < E && mk[e]) ? (R)rb[e] : (R)0);
         }
+        X.zero_ends(buf, rows, st);
+        __syncthreads();
+        dft_core<kWide, true>(X, buf, rows);
       }
     } else {
-#pragma unroll
-      for (int s = 0; s < kMaxPairs; ++s) {
-        const int pidx = threadIdx.x + s * kThreads;
-        if (pidx < rows * np) {
-          const int rr = pidx / np, k = pidx - rr * np;
-          const int kk = X.partner(k);
-          const C* row = buf + rr * st;
-          fwd_post_pair<R>(X, X.out(row, X.bin(k)), X.out(row, X.bin(kk)), k, kk, va[s][0],
-                           va[s][1], va[s][2], va[s][3]);
-        }
-      }
-    }
-    __syncthreads();
-    // 4. stage transposed in LDS: stg[k * G + jr]
-#pragma unroll
-    for (int s = 0; s < kMaxPairs; ++s) {
-      const int pidx = threadIdx.x + s * kThreads;
-      if (pidx < rows * np) {
+      const bool even = E == G * nx;             // the last group may hold one row less
+#pragma unroll 2
+      for (int pidx = threadIdx.x; pidx < rows * np; pidx += kThreads) {
         const int rr = pidx / np, k = pidx - rr * np;
         const int kk = X.partner(k);
-        stg[k * G + 2 * rr] = va[s][0];
-        stg[k * G + 2 * rr + 1] = va[s][1];
-        if (kk != k) {
-          stg[kk * G + 2 * rr] = va[s][2];
-          stg[kk * G + 2 * rr + 1] = va[s][3];
+        const C* row = buf + rr * st;
+        R xa, xb, xak, xbk;
+        fwd_post_pair<R>(X, X.out(row, X.bin(k)), X.out(row, X.bin(kk)), k, kk, xa, xb, xak,
+                         xbk);
+        const size_t o = (size_t)(2 * rr) * nx;
+        const int ja = 2 * rr;
+        if (even || j0 + ja < ny) {
+          t[o + k] = xa;
+          t[o + kk] = xak;
         }
-      }
-    }
-    __syncthreads();
-    // 5. coalesced transposed store (one loop per store kind: a store kind
-    //    chosen inside the loop body is merged away by the compiler)
-    BHX_GLOBAL R* t = (BHX_GLOBAL R*)I.t;
-    if (stream_t) {
-      for (int e = threadIdx.x; e < nx * G; e += kThreads) {
-        const int k = e / G, j = j0 + e - k * G;
-        if (j < ny) __builtin_nontemporal_store(stg[e], &t[(size_t)k * ny + j]);
-      }
-    } else {
-      for (int e = threadIdx.x; e < nx * G; e += kThreads) {
-        const int k = e / G, j = j0 + e - k * G;
-        if (j < ny) t[(size_t)k * ny + j] = stg[e];
+        if (even || j0 + ja + 1 < ny) {
+          t[o + nx + k] = xb;
+          t[o + nx + kk] = xbk;
+        }
       }
     }
     __syncthreads();
@@ -1525,173 +1532,629 @@ __global__ void __launch_bounds__(kThreads) k_rowfwd(const Batch* __restrict__ B
 }
 
 // ---------------------------------------------------------------------------
-// Column passes on the transposed buffer t ([nx][nz][ny], y fastest).  A
-// pencil is a line of t along y (contiguous) or, in three dimensions, along z
-// (stride ny); the pencils of one item are transformed two to a complex FFT.
-//   kCol2D    forward along y, scale by 1/(lambda_x + lambda_y)^2, inverse;
-//   kColYFwd  forward along y (three dimensions);
-//   kColZ     forward along z, scale by 1/(lambda_x + lambda_y + lambda_z)^2,
-//             inverse along z;
-//   kColYInv  inverse along y.
-// All in place on t.  SP: compile-time shape of the pass's axis and pencil
-// group (see XPlan), 0 for any shape.
+// Column solve: t <- (lambda I + T)^-2 t along the last axis of every column
+// of t (y in two dimensions, z in three), lambda the column's eigenvalue sum
+// of the transformed axes and T the second difference of the axis.  This is
+// the whole column part of the preconditioner, exactly: after the transforms
+// of the other axes the operator is block diagonal with these tridiagonal
+// (periodic: cyclic) blocks, so no transform along the last axis is needed.
+//
+// T + lambda I has constant coefficients and factors into two first-order
+// recursions, (1/rho) (1 - rho S)(1 - rho S^-1) with S the shift and rho < 1
+// the root of rho + 1/rho = 2 + lambda; the boundary rule only sets the state
+// a recursion enters with.  Periodic and Neumann axes run (1 - rho S)^-2
+// downwards, then (1 - rho S^-1)^-2 upwards; the entry states follow from the
+// periodic (even) extension in closed form.  Dirichlet axes run the pivots of
+// the tridiagonal's LDL^T factorisation, which are ratios of
+// W_i = 1 - rho^(2(i+1)), so that each recursion starts from 0.  The one
+// column with lambda = 0 (no Dirichlet rule on the transformed axes) is solved
+// by running sums, the constant mode removed (Neumann, periodic).
+//
+// A block stages W neighbouring columns in LDS (t is read and written once, in
+// runs of W elements).  A column is then one wave's (COLS = 1) or a sixteenth
+// lane row's (COLS = 4): each lane keeps LC consecutive rows in registers, and
+// the lanes' segments meet through their recursion states, scanned with the
+// vector unit's own lane moves (DPP).  No barrier but around the staging.
+//
+// Bound: memory and launch latency up to about 1024^2 nodes, HBM beyond (16
+// bytes and about 20 operations per node in FP64).  The transforms it replaces
+// cost two FFTs per column, four of twice the length where Bluestein runs.
+// Relative to the spectral form its rounding is smaller in the energy norm
+// that conjugate gradients work in (about 1e-11 against 1e-10 at 2048 nodes
+// and the smallest lambda).
+// ---------------------------------------------------------------------------
+
+// DPP lane moves of a double; lanes without a source read 0.
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+  union { double d; int i[2]; } a, b;
+  a.d = v;
+  b.i[0] = __builtin_amdgcn_update_dpp(0, a.i[0], CTRL, 0xf, 0xf, true);
+  b.i[1] = __builtin_amdgcn_update_dpp(0, a.i[1], CTRL, 0xf, 0xf, true);
+  return b.d;
+}
+constexpr int kRowShl = 0x100, kRowShr = 0x110;      // + lanes, within rows of 16
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  union { double d; int i[2]; } a, b;
+  a.d = v;
+  b.i[0] = __builtin_amdgcn_readlane(a.i[0], lane);
+  b.i[1] = __builtin_amdgcn_readlane(a.i[1], lane);
+  return b.d;
+}
+
+// sqrt(x), x > 0, from the hardware estimate of 1 / sqrt(x) by two Newton-
+// Raphson steps and a correction of the root.
+__device__ __forceinline__ double root(double x) {
+  double r = __builtin_amdgcn_rsq(x);
+  r = fma(0.5 * r, fma(-x * r, r, 1.0), r);
+  r = fma(0.5 * r, fma(-x * r, r, 1.0), r);
+  const double s = x * r;
+  return fma(0.5 * r, fma(-s, s, x), s);
+}
+// 1 - (1 - d)^n by binary powering of m = 1 - (1 - d)^k: every step adds
+// positive terms, so small results keep their relative accuracy.
+__device__ __forceinline__ double one_minus_pow(double d, int n) {
+  double m = 0.0;
+#pragma unroll 1
+  for (int b = 12; b >= 0; --b) {
+    m = m * (2.0 - m);
+    m = fma(((n >> b) & 1) ? d : 0.0, 1.0 - m, m);
+  }
+  return m;
+}
+// x^n by binary powering.
+__device__ __forceinline__ double int_pow(double x, int n) {
+  double r = 1.0;
+#pragma unroll 1
+  for (; n; n >>= 1) {
+    r *= (n & 1) ? x : 1.0;
+    x *= x;
+  }
+  return r;
+}
+
+// How a column of n rows lies in its lanes: LC rows per lane, nseg lanes in
+// use; the last one misses `m` rows, which count as zeros.  A wave's rows of 16
+// lanes are the stages of the scan: `row` (0 if COLS = 4) and place in it.
+template <int LC, int COLS>
+struct ColCut {
+  int nseg, m, last, nl;     // last: row of the last segment; nl: segments in that row
+  int li, l16, row;          // this lane: segment, place in its row, row of the column
+  int below;                 // existing segments of its row after it
+  __device__ __forceinline__ ColCut(int n) {
+    const int lane = threadIdx.x & 63;
+    nseg = (n + LC - 1) / LC;
+    m = nseg * LC - n;
+    last = (nseg - 1) >> 4;
+    nl = nseg - 16 * last;
+    l16 = lane & 15;
+    row = COLS == 1 ? lane >> 4 : 0;
+    li = 16 * row + l16;
+    below = max(min(15, nseg - 1 - 16 * row) - l16, 0);
+  }
+  // value of lane `s` of the lane's own row
+  __device__ __forceinline__ double in_row(double v, int s) const {
+    return __shfl(v, ((int)threadIdx.x & 48) + s, 64);
+  }
+};
+
+// rho^LC and its powers over 1, 2, 4, 8, 16 segments.
+struct ColPow {
+  double p[5];
+  __device__ __forceinline__ ColPow(double pl) {
+    p[0] = pl;
+#pragma unroll
+    for (int k = 1; k < 5; ++k) p[k] = p[k - 1] * p[k - 1];
+  }
+  // over s segments, s <= 15
+  __device__ __forceinline__ double over(int s) const {
+    double r = 1.0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) r *= ((s >> k) & 1) ? p[k] : 1.0;
+    return r;
+  }
+};
+
+// Inclusive scan of the states within rows of 16 lanes, from the states of
+// each segment alone.  TWO: second-order states (else s1 alone).
+template <int LC, bool UP, bool TWO>
+__device__ __forceinline__ void row_scan(const ColPow& P, double& s1, double& s2) {
+  double len = LC;
+  auto step = [&](double x1, double x2, double p) {
+    if (TWO) s2 = fma(p, fma(len, x1, x2), s2);
+    s1 = fma(p, x1, s1);
+    len += len;
+  };
+  step(UP ? dpp<kRowShl + 1>(s1) : dpp<kRowShr + 1>(s1),
+       !TWO ? 0.0 : UP ? dpp<kRowShl + 1>(s2) : dpp<kRowShr + 1>(s2), P.p[0]);
+  step(UP ? dpp<kRowShl + 2>(s1) : dpp<kRowShr + 2>(s1),
+       !TWO ? 0.0 : UP ? dpp<kRowShl + 2>(s2) : dpp<kRowShr + 2>(s2), P.p[1]);
+  step(UP ? dpp<kRowShl + 4>(s1) : dpp<kRowShr + 4>(s1),
+       !TWO ? 0.0 : UP ? dpp<kRowShl + 4>(s2) : dpp<kRowShr + 4>(s2), P.p[2]);
+  step(UP ? dpp<kRowShl + 8>(s1) : dpp<kRowShr + 8>(s1),
+       !TWO ? 0.0 : UP ? dpp<kRowShl + 8>(s2) : dpp<kRowShr + 8>(s2), P.p[3]);
+}
+
+// The recursions over a lane's segment: downwards (l up) or upwards from the
+// states (s1, s2); x <- s2 if STORE.
+template <int LC, bool UP, bool STORE>
+__device__ __forceinline__ void col_sweep(double (&v)[LC], double rho, double& s1, double& s2) {
+#pragma unroll
+  for (int k = 0; k < LC; ++k) {
+    const int l = UP ? LC - 1 - k : k;
+    s1 = fma(rho, s1, v[l]);
+    s2 = fma(rho, s2, s1);
+    if (STORE) v[l] = s2;
+  }
+}
+template <int LC>
+__device__ __forceinline__ void col_clear_tail(double (&v)[LC], int len) {
+  if (len >= LC) return;
+#pragma unroll
+  for (int l = 0; l < LC; ++l) v[l] = l < len ? v[l] : 0.0;
+}
+
+// Aggregates of the column's rows of 16 lanes, per lane of the column (rows
+// past the last are unused).
+template <int LC, int COLS, bool UP, bool TWO>
+struct RowAgg {
+  static constexpr int N = COLS == 1 ? 4 : 1;
+  double a1[N], a2[N];
+  __device__ __forceinline__ RowAgg(const ColCut<LC, COLS>& K, double s1, double s2) {
+    if constexpr (COLS == 1) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int at = 16 * r + (UP ? 0 : r == K.last ? K.nl - 1 : 15);
+        a1[r] = lane_value(s1, at);
+        a2[r] = TWO ? lane_value(s2, at) : 0.0;
+      }
+    } else {
+      a1[0] = K.in_row(s1, UP ? 0 : K.nl - 1);
+      a2[0] = TWO ? K.in_row(s2, UP ? 0 : K.nl - 1) : 0.0;
+    }
+  }
+  // Takes the states (x1, x2) through the column; `pick` receives the states
+  // that enter this lane's row.
+  __device__ __forceinline__ void through(const ColCut<LC, COLS>& K, const ColPow& P, double plast,
+                                          double& x1, double& x2, double& e1, double& e2) const {
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      const int r = UP ? N - 1 - k : k;
+      if (r <= K.last) {
+        if (r == K.row) {
+          e1 = x1;
+          e2 = x2;
+        }
+        const double p = r == K.last ? plast : P.p[4];
+        const double len = r == K.last ? LC * K.nl : LC * 16;
+        if (TWO) x2 = fma(p, fma(len, x1, x2), a2[r]);
+        x1 = fma(p, x1, a1[r]);
+      }
+    }
+  }
+};
+
+// Neumann and periodic axes.
+template <int LC, int COLS>
+__device__ __forceinline__ void col_even(double (&v)[LC], int n, bool neumann,
+                                         const ColCut<LC, COLS>& K, int len, double pa) {
+  const double rho = recip(1.0 + pa);
+  double pl = rho;
+#pragma unroll
+  for (int l = 1; l < LC; l <<= 1) pl *= pl;
+  const ColPow P(pl);
+  const double plast = K.nl == 16 ? P.p[4] : P.over(K.nl);
+  // rho^-m, rho^n and, with q = rho^period, 1 / (1 - q), 1 / (1 - rho) and
+  // 1 / (1 - rho^2) from one reciprocal
+  const double m = K.m, im = int_pow(1.0 + pa, K.m);
+  const double pn = int_pow(P.p[4], K.last) * plast * im;
+  const double q = neumann ? pn * pn : pn, per = neumann ? 2.0 * n : (double)n;
+  const double iall = recip((1.0 - q) * pa * (1.0 + rho));
+  const double iq = iall * pa * (1.0 + rho);
+  const double id = (1.0 + pa) * iall * (1.0 - q) * (1.0 + rho);
+  const double id2 = id * iall * (1.0 - q) * pa;
+  const double pe = P.over(K.l16), pb = P.over(K.below);
+  const double le = LC * K.l16, lb = LC * K.below;
+#pragma unroll
+  for (int l = 0; l < LC; ++l) v[l] *= rho * rho;
+  // 1. aggregates from zero states: downwards and, for the even extension,
+  //    upwards; the states entering the column from its extension
+  double c1 = 0.0, c2 = 0.0;
+  col_sweep<LC, false, false>(v, rho, c1, c2);
+  row_scan<LC, false, true>(P, c1, c2);
+  const RowAgg<LC, COLS, false, true> C(K, c1, c2);
+  double x1 = 0.0, x2 = 0.0, e1 = 0.0, e2 = 0.0;
+  C.through(K, P, plast, x1, x2, e1, e2);
+  x1 *= im;                                  // before the missing rows
+  x2 = fma(x2, im, -m * x1);
+  if (neumann) {
+    double b1 = 0.0, b2 = 0.0, y1 = 0.0, y2 = 0.0;
+    col_sweep<LC, true, false>(v, rho, b1, b2);
+    row_scan<LC, true, true>(P, b1, b2);
+    const RowAgg<LC, COLS, true, true> U(K, b1, b2);
+    U.through(K, P, plast, y1, y2, e1, e2);
+    x2 = fma(pn, fma((double)n, x1, x2), y2);
+    x1 = fma(pn, x1, y1);
+  }
+  double a1 = x1 * iq;
+  double a2 = fma(per * q * iq, a1, x2 * iq);
+  C.through(K, P, plast, a1, a2, e1, e2);
+  // 2. downwards with the true states
+  c1 = fma(pe, e1, dpp<kRowShr + 1>(c1));
+  c2 = fma(pe, fma(le, e1, e2), dpp<kRowShr + 1>(c2));
+  col_sweep<LC, false, true>(v, rho, c1, c2);
+  col_clear_tail<LC>(v, len);
+  // 3. aggregates upwards; the states entering from beyond the last row
+  double b1 = 0.0, b2 = 0.0;
+  col_sweep<LC, true, false>(v, rho, b1, b2);
+  row_scan<LC, true, true>(P, b1, b2);
+  const RowAgg<LC, COLS, true, true> U(K, b1, b2);
+  double d1, d2;
+  if (neumann) {
+    // the solution and its half-way state are even about the boundary
+    a1 *= im;
+    a2 = fma(a2, im, -m * a1);
+    d1 = fma(rho, a2, a1 * id) * id2;
+    d2 = fma(rho, d1, a2) * id;
+  } else {
+    x1 = x2 = 0.0;
+    U.through(K, P, plast, x1, x2, e1, e2);
+    d1 = x1 * iq;
+    d2 = fma(per * q * iq, d1, x2 * iq);
+  }
+  d1 *= im;                                  // past the missing rows
+  d2 = fma(d2, im, -m * d1);
+  U.through(K, P, plast, d1, d2, e1, e2);
+  // 4. upwards
+  b1 = fma(pb, e1, dpp<kRowShl + 1>(b1));
+  b2 = fma(pb, fma(lb, e1, e2), dpp<kRowShl + 1>(b2));
+  col_sweep<LC, true, true>(v, rho, b1, b2);
+}
+
+// Dirichlet axes: with W_i = 1 - rho^(2(i+1)) the LDL^T sweeps of T + lambda
+// are C_i = W_i f_i + rho C_(i-1) downwards and y_i = rho (G_i + y_(i+1)),
+// G_i = C_i / (W_i W_(i+1)), upwards, from zero states; the solution is
+// W_i y_i.  Two applications.
+template <int LC, int COLS>
+__device__ __forceinline__ void col_odd(double (&v)[LC], const ColCut<LC, COLS>& K, int len,
+                                        double pa) {
+  const double rho = recip(1.0 + pa);
+  const double r2 = rho * rho, d2 = pa * rho * (1.0 + rho);   // W_(i+1) = r2 W_i + d2
+  const double w0 = one_minus_pow(d2, K.li * LC + 1);         // W of the segment's first row
+  double pl = rho;
+#pragma unroll
+  for (int l = 1; l < LC; l <<= 1) pl *= pl;
+  const ColPow P(pl);
+  const double plast = K.nl == 16 ? P.p[4] : P.over(K.nl);
+  const double pe = P.over(K.l16), pb = P.over(K.below);
+#pragma unroll 1
+  for (int rep = 0; rep < 2; ++rep) {
+    // (the W_i are formed anew in each sweep: kept, they would take as many
+    // registers as the rows)
+    double wi = w0, cs = 0.0, ys = 0.0, none = 0.0, x1 = 0.0, e1 = 0.0;
+    asm volatile("" : "+v"(wi));
+#pragma unroll
+    for (int l = 0; l < LC; ++l) {
+      v[l] *= wi;
+      cs = fma(rho, cs, v[l]);
+      wi = fma(r2, wi, d2);
+    }
+    row_scan<LC, false, false>(P, cs, none);
+    const RowAgg<LC, COLS, false, false> C(K, cs, none);
+    C.through(K, P, plast, x1, none, e1, none);
+    cs = fma(pe, e1, dpp<kRowShr + 1>(cs));
+    wi = w0;
+    asm volatile("" : "+v"(wi));
+#pragma unroll
+    for (int l = 0; l < LC; ++l) {
+      cs = fma(rho, cs, v[l]);
+      const double wn = fma(r2, wi, d2);
+      v[l] = cs * recip(wi * wn);
+      wi = wn;
+    }
+    col_clear_tail<LC>(v, len);
+#pragma unroll
+    for (int l = LC - 1; l >= 0; --l) ys = rho * (v[l] + ys);
+    row_scan<LC, true, false>(P, ys, none);
+    const RowAgg<LC, COLS, true, false> U(K, ys, none);
+    x1 = 0.0;                                // nothing enters the last segment
+    U.through(K, P, plast, x1, none, e1, none);
+    ys = fma(pb, e1, dpp<kRowShl + 1>(ys));
+#pragma unroll
+    for (int l = LC - 1; l >= 0; --l) {
+      ys = rho * (v[l] + ys);
+      v[l] = ys;
+    }
+    wi = w0;
+    asm volatile("" : "+v"(wi));
+#pragma unroll
+    for (int l = 0; l < LC; ++l) {
+      v[l] *= wi;
+      wi = fma(r2, wi, d2);
+    }
+    col_clear_tail<LC>(v, len);
+  }
+}
+
+// Running sum of v over the lanes of a column, without the lane's own value,
+// and the column's total.
+template <int COLS>
+__device__ __forceinline__ double col_running_sum(double v, double& total) {
+  const int lane = threadIdx.x & 63;
+  double x = v;
+  x += dpp<kRowShr + 1>(x);
+  x += dpp<kRowShr + 2>(x);
+  x += dpp<kRowShr + 4>(x);
+  x += dpp<kRowShr + 8>(x);
+  double s = dpp<kRowShr + 1>(x);
+  if constexpr (COLS == 1) {
+    const double r0 = lane_value(x, 15), r1 = lane_value(x, 31), r2 = lane_value(x, 47),
+                 r3 = lane_value(x, 63);
+    s += lane < 16 ? 0.0 : lane < 32 ? r0 : lane < 48 ? r0 + r1 : r0 + r1 + r2;
+    total = r0 + r1 + (r2 + r3);
+  } else {
+    total = __shfl(x, (lane & 48) + 15, 64);
+  }
+  return s;
+}
+
+// The column with lambda = 0: T^+ T^+ (Neumann, periodic: the constant mode
+// removed) or T^-2 (Dirichlet).  T u = f has fluxes g_i = u_i - u_(i+1): g is
+// the running sum of f (less its mean) plus a constant, u minus the running
+// sum of g plus a constant.
+template <int LC, int COLS>
+__device__ __forceinline__ void col_zero(double (&v)[LC], int n, int bc, int j0, int len) {
+  const double inv = recip(bc == kDirichlet ? n + 1.0 : (double)n);
+  double total;
+#pragma unroll 1
+  for (int rep = 0; rep < 2; ++rep) {
+    double a = 0.0, j = j0;
+    asm volatile("" : "+v"(j));          // (row numbers counted, not kept)
+#pragma unroll
+    for (int l = 0; l < LC; ++l) {
+      a += v[l];
+      v[l] = a;
+    }
+    const double x = col_running_sum<COLS>(a, total);
+    const double mean = bc == kDirichlet ? 0.0 : total * inv;
+#pragma unroll
+    for (int l = 0; l < LC; ++l) {
+      j += 1.0;
+      v[l] = fma(-mean, j, x + v[l]);
+    }
+    col_clear_tail<LC>(v, len);
+    a = 0.0;
+#pragma unroll
+    for (int l = 0; l < LC; ++l) {
+      const double g = v[l];
+      v[l] = a;
+      a += g;
+    }
+    const double y = col_running_sum<COLS>(a, total);
+    const double c = bc == kNeumann ? 0.0 : total * inv;
+    j = j0;
+    asm volatile("" : "+v"(j));
+#pragma unroll
+    for (int l = 0; l < LC; ++l) {
+      j += 1.0;
+      v[l] = fma(c, j, -(y + v[l]));
+    }
+    col_clear_tail<LC>(v, len);
+  }
+  if (bc != kDirichlet) {
+    double a = 0.0;
+#pragma unroll
+    for (int l = 0; l < LC; ++l) a += v[l];
+    col_running_sum<COLS>(a, total);
+    const double mean = total * inv;
+#pragma unroll
+    for (int l = 0; l < LC; ++l) v[l] -= mean;
+  }
+}
+
+// One item: COLS columns a wave, 8 COLS columns from column c * 8 COLS.
+// Staged as tile[column * cs + row + row / LC], cs = col_stride.
+template <typename R, int LC, int COLS, bool ODD, bool d3>
+__device__ __forceinline__ void col_item(R* tile, const Batch& B, const Inst& I, int c, bool zero) {
+  constexpr int W = kColWaves * COLS;                // columns of the item
+  constexpr int NR = kColThreads / W;                // rows staged at a time
+  constexpr int NL = LC * (COLS == 1 ? 64 : 16) / NR;   // of them, at most
+  // slots between rows NR apart (k of them); a row's own pad slots
+  constexpr auto slots = [](int k) { return k * NR + (LC == 1 ? 0 : k * NR / LC); };
+  const int n = d3 ? I.nz : I.ny, bc = d3 ? I.bcz : I.bcy;
+  const int ncol = d3 ? I.nx * I.ny : I.nx;
+  const int cs = col_stride(n, LC, W);
+  const int e0 = c * W;
+  // (opaque, so that nothing derived from it is kept from item to item)
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  // 1. stage the columns; a thread's rows are NR apart
+  const int gc = tid % W, gr = tid / W;
+  BHX_GLOBAL R* tg =
+      (BHX_GLOBAL R*)I.t + (size_t)min(gr, n - 1) * ncol + min(e0 + gc, ncol - 1);
+  const size_t step = (size_t)NR * ncol;
+  R raw[NL];
+  {
+    BHX_GLOBAL const R* a = tg;
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+      if (k * NR < n) raw[k] = *a;
+      a += gr + (k + 1) * NR < n ? step : 0;         // rows past the end: the last one again
+    }
+  }
+  // the eigenvalue of the lane's column
+  const int lane = tid & 63, wv = tid >> 6;
+  const int cl = wv * COLS + (COLS == 1 ? 0 : lane >> 4);
+  const int e = e0 + cl, ec = min(e, ncol - 1);
+  BHX_GLOBAL const double* rt = (BHX_GLOBAL const double*)B.rtab[0];
+  double lam = rt[I.lamx + (d3 ? ec % I.nx : ec)];
+  if (d3) lam += rt[I.lamy + ec / I.nx];
+  if (I.ctl->done) return;                           // (nothing changes it during this pass)
+  const bool special = zero && e == 0;
+  if (special) lam = 1.0;
+  // rho = 1 / (1 + pa); 1 - rho = pa rho keeps its relative accuracy for small
+  // lambda
+  const double pa = 0.5 * (lam + root(lam * (lam + 4.0)));
+  R* tl = tile + gc * cs + gr + (LC == 1 ? 0 : gr / LC);
+  __syncthreads();                                   // the previous item's stores have read it
+#pragma unroll
+  for (int k = 0; k < NL; ++k) {
+    if ((k + 1) * NR <= n) tl[slots(k)] = raw[k];
+    else if (gr + k * NR < n) tl[slots(k)] = raw[k];
+  }
+  __syncthreads();
+  // 2. the lane's segment
+  const ColCut<LC, COLS> K(n);
+  const int j0 = K.li * LC, len = min(max(n - j0, 0), LC);
+  R* ts = tile + cl * cs + (LC == 1 ? j0 : j0 + K.li);
+  auto fetch = [&](double (&v)[LC]) {
+#pragma unroll
+    for (int l = 0; l < LC; ++l) v[l] = 0.0;
+    if (len > 0) {
+#pragma unroll
+      for (int l = 0; l < LC; ++l) v[l] = (double)ts[l];
+    }
+    col_clear_tail<LC>(v, len);
+  };
+  auto put = [&](const double (&v)[LC], bool on) {
+    if (on && len > 0) {
+#pragma unroll
+      for (int l = 0; l < LC; ++l) ts[l] = (R)v[l];
+    }
+  };
+  const bool wave0 = zero && c == 0 && wv == 0;      // holds the column lambda = 0
+  if (!(COLS == 1 && wave0)) {
+    double v[LC];
+    fetch(v);
+    if constexpr (ODD) col_odd<LC, COLS>(v, K, len, pa);
+    else col_even<LC, COLS>(v, n, bc == kNeumann, K, len, pa);
+    put(v, !special);
+  }
+  if (wave0) {
+    double v[LC];
+    fetch(v);
+    col_zero<LC, COLS>(v, n, bc, j0, len);
+    put(v, special);
+  }
+  __syncthreads();
+  // 3. back to t (addresses formed anew: kept, the loads' would take as many
+  // registers as the rows)
+  if (e0 + gc >= ncol) return;
+  asm volatile("" : "+v"(tg));
+#pragma unroll
+  for (int k = 0; k < NL; ++k) {
+    if ((k + 1) * NR <= n) *tg = tl[slots(k)];
+    else if (gr + k * NR < n) *tg = tl[slots(k)];
+    tg += step;
+  }
+}
+
+// PASS: the work list, kPassC (two dimensions) or kPassZ (three).  LONG: the
+// class of the longest column (col_class); the longer ones take twice the
+// registers, which would spill at the short ones' occupancy (and a kernel with
+// spills pays for its scratch memory at every launch).
+template <typename R, int PASS, int LONG>
+__global__ void __launch_bounds__(kColThreads, LONG ? 2 : 4)
+    k_colsolve(const Batch* __restrict__ Bp, int count_iter) {
+  constexpr bool d3 = PASS == kPassZ;
+  const Batch B = *(BHX_CONST const Batch*)Bp;   // scalar loads, kept in registers
+  extern __shared__ __align__(16) unsigned char smem[];
+  debug_fill_lds(smem);
+  R* tile = (R*)smem;
+  for (int itm = logical_block(); itm < B.n_items[PASS]; itm += gridDim.x) {
+    const int code = item_code(B, PASS, itm);
+    const Inst I = B.inst[code >> kItemShift];
+    const int c = code & kItemMask;
+    BHX_GLOBAL Ctl* ctl = I.ctl;
+    const bool zero = I.bcx != kDirichlet && (!d3 || I.bcy != kDirichlet);
+    const int lc = col_rows(d3 ? I.nz : I.ny, d3 ? I.Gz : I.Gc);
+    const bool wide = (d3 ? I.Gz : I.Gc) == 4 * kColWaves;
+    const bool odd = (d3 ? I.bcz : I.bcy) == kDirichlet;
+#define BHX_COL(LC)                                                        \
+  case LC:                                                                 \
+    if (wide) {                                                            \
+      if (odd) col_item<R, LC, 4, true, d3>(tile, B, I, c, zero);          \
+      else col_item<R, LC, 4, false, d3>(tile, B, I, c, zero);             \
+    } else {                                                               \
+      if (odd) col_item<R, LC, 1, true, d3>(tile, B, I, c, zero);          \
+      else col_item<R, LC, 1, false, d3>(tile, B, I, c, zero);             \
+    }                                                                      \
+    break;
+    switch (lc) {
+      BHX_COL(1)
+      BHX_COL(2)
+      BHX_COL(4)
+      BHX_COL(8)
+      default:
+        if constexpr (LONG > 0) {
+          switch (lc) { BHX_COL(16) BHX_COL(32) }
+        }
+        // FP32 axes of more than 2048 nodes (no Dirichlet axis is that long)
+        if constexpr (LONG > 1)
+          if (lc > 32) col_item<R, 64, 1, false, d3>(tile, B, I, c, zero);
+        break;
+    }
+#undef BHX_COL
+    if (count_iter && c == 0 && threadIdx.x == 0 && !ctl->done) ctl->iter = ctl->iter + 1;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Transforms along y in three dimensions, in place on t ([nz][ny][nx], x
+// fastest): forward before the column solve along z (kColYFwd), inverse after
+// it (kColYInv).  An item is Gc neighbouring pencils (one z, consecutive kx),
+// transformed two to a complex FFT; loads and stores go index-major, so a
+// wave touches runs of Gc elements.  SP: compile-time shape of the axis and
+// pencil group (see XPlan), 0 for any shape.
 // ---------------------------------------------------------------------------
 
 template <typename R, int KIND, int SP, int FAM = 0>
-__global__ void __launch_bounds__(kThreads) k_col(const Batch* __restrict__ Bp, int count_iter,
-                                                  int twoff) {
+__global__ void __launch_bounds__(kThreads) k_ypass(const Batch* __restrict__ Bp, int twoff) {
   using C = typename V2<R>::T;
-  constexpr bool CZ = FAM == kFamCz;
   constexpr bool kWide = FAM != kFamNarrow;
-  constexpr int kPass = KIND == kColZ ? kPassZ : kPassC;
-  constexpr bool kStrided = KIND == kColZ;       // z pencils: stride ny
-  constexpr bool kScale = KIND == kCol2D || KIND == kColZ;
   const Batch B = *(BHX_CONST const Batch*)Bp;   // scalar loads, kept in registers
   extern __shared__ __align__(16) unsigned char smem[];
   debug_fill_lds(smem);
   C* buf = (C*)smem;
   R* stg = (R*)smem;
   C* twl = buf + twoff;
-  __shared__ R s_lam[kMaxGc];      // per pencil: eigenvalue sum of the other axes
   int staged = -1;
-  for (int itm = logical_block(); itm < B.n_items[kPass]; itm += gridDim.x) {
-    const int code = item_code(B, kPass, itm);
+  for (int itm = logical_block(); itm < B.n_items[kPassC]; itm += gridDim.x) {
+    const int code = item_code(B, kPassC, itm);
     const Inst I = B.inst[code >> kItemShift];
     const int c = code & kItemMask;
     BHX_GLOBAL Ctl* ctl = I.ctl;
-    BHX_GLOBAL R* t = (BHX_GLOBAL R*)I.t;
     // 1. the item's pencils: cnt <= Gp of length n; element j of pencil cr at
-    //    t[pb + cr * ps + j * js]
-    int n, Gp, cnt, ps, js, plan, c0 = 0, kx = 0, ky0 = 0;
-    size_t pb;
-    if constexpr (kStrided) {
-      n = SP ? sp_nodes(SP) : I.nz;
-      Gp = SP ? SP >> 8 : I.Gz;
-      plan = I.planz;
-      const int ngy = (I.ny + Gp - 1) / Gp;
-      kx = c / ngy;
-      ky0 = (c - kx * ngy) * Gp;
-      cnt = min(Gp, I.ny - ky0);
-      pb = (size_t)kx * I.nz * I.ny + ky0;
-      ps = 1;
-      js = I.ny;
-    } else {
-      n = SP ? sp_nodes(SP) : I.ny;
-      Gp = SP ? SP >> 8 : I.Gc;
-      plan = I.plany;
-      c0 = c * Gp;
-      cnt = min(Gp, I.nx * I.nz - c0);    // pencils (kx, z); nz = 1 in two dimensions
-      pb = (size_t)c0 * n;
-      ps = n;
-      js = 1;
-    }
-    // element e of the load/store order -> (pencil, index): y pencils
-    // pencil-major; z pencils index-major, so neighbouring lanes touch
-    // neighbouring pencils, adjacent in memory
+    //    t[cr + j * js]
+    const int n = SP ? sp_nodes(SP) : I.ny, Gp = SP ? SP >> 8 : I.Gc;
+    const int ngx = (I.nx + Gp - 1) / Gp;
+    const int z = c / ngx, kx0 = (c - z * ngx) * Gp;
+    const int cnt = min(Gp, I.nx - kx0), js = I.nx;
+    BHX_GLOBAL R* t = (BHX_GLOBAL R*)I.t + (size_t)z * n * js + kx0;
     auto split = [&](int e, int& cr, int& j) {
-      if constexpr (kStrided) {
-        j = e / Gp;
-        cr = e - j * Gp;
-      } else {
-        cr = e / n;
-        j = e - cr * n;
-      }
+      j = e / Gp;
+      cr = e - j * Gp;
     };
-    auto at = [&](int cr, int j) { return pb + (size_t)cr * ps + (size_t)j * js; };
+    auto at = [&](int cr, int j) { return cr + (size_t)j * js; };
     const int Et = Gp * n;
-    //    issue together: the first kPre loads of the item, the eigenvalues of
-    //    its pencils and `done` (unchanged during the pass); then stage the
-    //    plan tables
+    //    issue together: the first kPre loads of the item and `done`
+    //    (unchanged during the pass); then stage the plan tables
     R tv[kPre];
 #pragma unroll
     for (int u = 0; u < kPre; ++u) {
       int cr, j;
       split(min((int)threadIdx.x + u * kThreads, Et - 1), cr, j);
-      tv[u] = t[cr < cnt ? at(cr, j) : pb];
-    }
-    R lam = (R)0;
-    if constexpr (KIND == kCol2D) {
-      const XPlan<R> Xx(B, I.planx);
-      lam = Xx.lam[min(c0 + min((int)threadIdx.x, kMaxGc - 1), I.nx - 1)];
-    } else if constexpr (KIND == kColZ) {
-      const XPlan<R> Xx(B, I.planx);
-      const XPlan<R> Xy(B, I.plany);
-      lam = Xx.lam[kx] + Xy.lam[min(ky0 + min((int)threadIdx.x, kMaxGc - 1), I.ny - 1)];
+      tv[u] = t[at(min(cr, cnt - 1), j)];
     }
     if (ctl->done) continue;
-    XPlan<R, SP> X(B, plan);
-    if constexpr (!CZ) X.cz = 0;   // chirp-z axes run on the CZ instances only
-    X.stage(twl, plan, staged, kScale);
+    XPlan<R, SP> X(B, I.plany);
+    X.cz = 0;                        // no chirp-z axis in three dimensions
+    X.stage(twl, I.plany, staged, false);
     const int rows = Gp >> 1;
     const int st = X.stride();
     const int np = X.pairs();
-    if constexpr (KIND == kCol2D && SP == 0) {
-      if (X.cz) {
-        // chirp-z DST-I along y: the first pencil of each pair, then the
-        // second, each through forward, scale and inverse (the DST-I is its
-        // own inverse) in the pair's row
-        if (threadIdx.x < kMaxGc) s_lam[threadIdx.x] = lam;
-#pragma unroll 1
-        for (int h = 0; h < 2; ++h) {
-          for (int e = threadIdx.x; e < Et; e += kThreads) {
-            int cr, j;
-            split(e, cr, j);
-            if ((cr & 1) == h) X.put_cz(buf + (cr >> 1) * st, j, cr < cnt ? t[at(cr, j)] : (R)0);
-          }
-          X.zero_ends(buf, rows, st);
-          __syncthreads();
-          dft_core<kWide>(X, buf, rows);
-          R ys[kMaxPairs][2];
-#pragma unroll
-          for (int s = 0; s < kMaxPairs; ++s) {
-            const int pidx = threadIdx.x + s * kThreads;
-            if (pidx < rows * np) {
-              const int rr = pidx / np, k = pidx - rr * np;
-              const int kk = X.partner(k);
-              const C* row = buf + rr * st;
-              const R la = s_lam[2 * rr + h];
-              R lk, lkk;
-              X.lam_pair(k, kk, lk, lkk);
-              ys[s][0] = X.coef_cz(row, k) * inv_sq<R>(la + lk);
-              ys[s][1] = X.coef_cz(row, kk) * inv_sq<R>(la + lkk);
-            }
-          }
-          __syncthreads();
-#pragma unroll
-          for (int s = 0; s < kMaxPairs; ++s) {
-            const int pidx = threadIdx.x + s * kThreads;
-            if (pidx < rows * np) {
-              const int rr = pidx / np, k = pidx - rr * np;
-              const int kk = X.partner(k);
-              X.put_cz(buf + rr * st, k, ys[s][0]);
-              if (kk != k) X.put_cz(buf + rr * st, kk, ys[s][1]);
-            }
-          }
-          X.zero_ends(buf, rows, st);
-          __syncthreads();
-          dft_core<kWide>(X, buf, rows);
-#pragma unroll
-          for (int s = 0; s < kMaxPairs; ++s) {
-            const int pidx = threadIdx.x + s * kThreads;
-            if (pidx < rows * np) {
-              const int rr = pidx / np, k = pidx - rr * np;
-              const int kk = X.partner(k);
-              const int cr = 2 * rr + h;
-              const C* row = buf + rr * st;
-              if (cr < cnt) {
-                t[at(cr, k)] = X.coef_cz(row, k);
-                if (kk != k) t[at(cr, kk)] = X.coef_cz(row, kk);
-              }
-            }
-          }
-          __syncthreads();
-        }
-        if (count_iter && c == 0 && threadIdx.x == 0) ctl->iter = ctl->iter + 1;
-        continue;
-      }
-    }
-    C vin[kMaxPairs][2];
-    if constexpr (KIND != kColYInv) {
+    R vin[kMaxPairs][4];
+    if constexpr (KIND == kColYFwd) {
       // 2. forward: place the pencils into the packed rows, FFT, spectra
       auto place = [&](int e, R v) {
         if (e >= Et) return;
@@ -1704,12 +2167,11 @@ __global__ void __launch_bounds__(kThreads) k_col(const Batch* __restrict__ Bp, 
       for (int e = threadIdx.x + kPre * kThreads; e < Et; e += kThreads) {
         int cr, j;
         split(e, cr, j);
-        place(e, t[cr < cnt ? at(cr, j) : pb]);
+        place(e, t[at(min(cr, cnt - 1), j)]);
       }
-      if (kScale && threadIdx.x < kMaxGc) s_lam[threadIdx.x] = lam;
       X.zero_ends(buf, rows, st);
       __syncthreads();
-      dft_core<kWide>(X, buf, rows);
+      dft_core<kWide, false>(X, buf, rows);
 #pragma unroll
       for (int s = 0; s < kMaxPairs; ++s) {
         const int pidx = threadIdx.x + s * kThreads;
@@ -1717,43 +2179,16 @@ __global__ void __launch_bounds__(kThreads) k_col(const Batch* __restrict__ Bp, 
           const int rr = pidx / np, k = pidx - rr * np;
           const int kk = X.partner(k);
           const C* row = buf + rr * st;
-          R xa, xb, xak, xbk;
-          fwd_post_pair<R>(X, X.out(row, X.bin(k)), X.out(row, X.bin(kk)), k, kk, xa, xb, xak,
-                           xbk);
-          if constexpr (KIND == kColYFwd) {
-            const int ca = 2 * rr, cb = ca + 1;
-            if (ca < cnt) {
-              t[at(ca, k)] = xa;
-              if (kk != k) t[at(ca, kk)] = xak;
-            }
-            if (cb < cnt) {
-              t[at(cb, k)] = xb;
-              if (kk != k) t[at(cb, kk)] = xbk;
-            }
-          } else {
-            // 3. scale by the inverse squared eigenvalue sums, inverse inputs
-            const R la = s_lam[2 * rr];
-            const R lb = s_lam[2 * rr + 1];
-            R lk, lkk;
-            X.lam_pair(k, kk, lk, lkk);
-            xa *= inv_sq<R>(la + lk);
-            xb *= inv_sq<R>(lb + lk);
-            xak *= inv_sq<R>(la + lkk);
-            xbk *= inv_sq<R>(lb + lkk);
-            inv_pre_pair<R>(X, xa, xb, xak, xbk, k, kk, vin[s][0], vin[s][1]);
-          }
+          fwd_post_pair<R>(X, X.out(row, X.bin(k)), X.out(row, X.bin(kk)), k, kk, vin[s][0],
+                           vin[s][1], vin[s][2], vin[s][3]);
         }
       }
-      if constexpr (KIND == kColYFwd) {
-        __syncthreads();
-        continue;
-      }
     } else {
-      // 2. inverse only: the spectra staged as stg[cr * n + k], inverse inputs
+      // 2. inverse: the spectra staged as stg[k * Gp + cr], inverse inputs
 #pragma unroll
       for (int u = 0; u < kPre; ++u) {
         const int e = threadIdx.x + u * kThreads;
-        if (e < Et) stg[e] = (e / n) < cnt ? tv[u] : (R)0;
+        if (e < Et) stg[e] = (e % Gp) < cnt ? tv[u] : (R)0;
       }
       for (int e = threadIdx.x + kPre * kThreads; e < Et; e += kThreads) {
         int cr, j;
@@ -1767,35 +2202,41 @@ __global__ void __launch_bounds__(kThreads) k_col(const Batch* __restrict__ Bp, 
         if (pidx < rows * np) {
           const int rr = pidx / np, k = pidx - rr * np;
           const int kk = X.partner(k);
-          const R* ra = stg + 2 * rr * n;
-          inv_pre_pair<R>(X, ra[k], ra[n + k], ra[kk], ra[n + kk], k, kk, vin[s][0], vin[s][1]);
+          C a, b;
+          inv_pre_pair<R>(X, stg[k * Gp + 2 * rr], stg[k * Gp + 2 * rr + 1],
+                          stg[kk * Gp + 2 * rr], stg[kk * Gp + 2 * rr + 1], k, kk, a, b);
+          vin[s][0] = a.x;
+          vin[s][1] = a.y;
+          vin[s][2] = b.x;
+          vin[s][3] = b.y;
         }
       }
-    }
-    __syncthreads();
+      __syncthreads();
 #pragma unroll
-    for (int s = 0; s < kMaxPairs; ++s) {
-      const int pidx = threadIdx.x + s * kThreads;
-      if (pidx < rows * np) {
-        const int rr = pidx / np, k = pidx - rr * np;
-        X.put_pair(buf + rr * st, k, X.partner(k), vin[s][0], vin[s][1]);
-      }
-    }
-    X.zero_ends(buf, rows, st);
-    __syncthreads();
-    dft_core<kWide>(X, buf, rows);
-    // 4. inverse outputs back into t
-    if (X.bc == kNeumann) {
-      for (int e = threadIdx.x; e < Et; e += kThreads) {
-        int cr, j;
-        split(e, cr, j);
-        if (cr < cnt) {
-          const C v = X.out(buf + (cr >> 1) * st, inv_index(j, n));
-          t[at(cr, j)] = (cr & 1) ? -v.y : v.x;
+      for (int s = 0; s < kMaxPairs; ++s) {
+        const int pidx = threadIdx.x + s * kThreads;
+        if (pidx < rows * np) {
+          const int rr = pidx / np, k = pidx - rr * np;
+          X.put_pair(buf + rr * st, k, X.partner(k), mk<C>(vin[s][0], vin[s][1]),
+                     mk<C>(vin[s][2], vin[s][3]));
         }
       }
-    } else {
-      // Hartley, DST-I: the inverse is the forward transform; reuse vin's registers
+      X.zero_ends(buf, rows, st);
+      __syncthreads();
+      dft_core<kWide, true>(X, buf, rows);
+      if (X.bc == kNeumann) {
+        for (int e = threadIdx.x; e < Et; e += kThreads) {
+          int cr, j;
+          split(e, cr, j);
+          if (cr < cnt) {
+            const C v = X.out(buf + (cr >> 1) * st, inv_index(j, n));
+            t[at(cr, j)] = (cr & 1) ? -v.y : v.x;
+          }
+        }
+        __syncthreads();
+        continue;
+      }
+      // Hartley, DST-I: the inverse is the forward transform
 #pragma unroll
       for (int s = 0; s < kMaxPairs; ++s) {
         const int pidx = threadIdx.x + s * kThreads;
@@ -1803,62 +2244,39 @@ __global__ void __launch_bounds__(kThreads) k_col(const Batch* __restrict__ Bp, 
           const int rr = pidx / np, k = pidx - rr * np;
           const int kk = X.partner(k);
           const C* row = buf + rr * st;
-          R a, b, ak, bk;
-          fwd_post_pair<R>(X, X.out(row, X.bin(k)), X.out(row, X.bin(kk)), k, kk, a, b, ak, bk);
-          vin[s][0] = mk<C>(a, b);
-          vin[s][1] = mk<C>(ak, bk);
-        }
-      }
-      if constexpr (kStrided) {
-        // through LDS, index-major (stg[k * Gp + cr]), for coalesced stores
-        __syncthreads();
-#pragma unroll
-        for (int s = 0; s < kMaxPairs; ++s) {
-          const int pidx = threadIdx.x + s * kThreads;
-          if (pidx < rows * np) {
-            const int rr = pidx / np, k = pidx - rr * np;
-            const int kk = X.partner(k);
-            stg[k * Gp + 2 * rr] = vin[s][0].x;
-            stg[k * Gp + 2 * rr + 1] = vin[s][0].y;
-            if (kk != k) {
-              stg[kk * Gp + 2 * rr] = vin[s][1].x;
-              stg[kk * Gp + 2 * rr + 1] = vin[s][1].y;
-            }
-          }
-        }
-        __syncthreads();
-        for (int e = threadIdx.x; e < Et; e += kThreads) {
-          int cr, j;
-          split(e, cr, j);
-          if (cr < cnt) t[at(cr, j)] = stg[e];
-        }
-      } else {
-#pragma unroll
-        for (int s = 0; s < kMaxPairs; ++s) {
-          const int pidx = threadIdx.x + s * kThreads;
-          if (pidx < rows * np) {
-            const int rr = pidx / np, k = pidx - rr * np;
-            const int kk = X.partner(k);
-            const int ca = 2 * rr, cb = ca + 1;
-            if (ca < cnt) {
-              t[at(ca, k)] = vin[s][0].x;
-              if (kk != k) t[at(ca, kk)] = vin[s][1].x;
-            }
-            if (cb < cnt) {
-              t[at(cb, k)] = vin[s][0].y;
-              if (kk != k) t[at(cb, kk)] = vin[s][1].y;
-            }
-          }
+          fwd_post_pair<R>(X, X.out(row, X.bin(k)), X.out(row, X.bin(kk)), k, kk, vin[s][0],
+                           vin[s][1], vin[s][2], vin[s][3]);
         }
       }
     }
-    if (count_iter && c == 0 && threadIdx.x == 0) ctl->iter = ctl->iter + 1;
+    // 3. through LDS, index-major (stg[k * Gp + cr]), for coalesced stores
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < kMaxPairs; ++s) {
+      const int pidx = threadIdx.x + s * kThreads;
+      if (pidx < rows * np) {
+        const int rr = pidx / np, k = pidx - rr * np;
+        const int kk = X.partner(k);
+        stg[k * Gp + 2 * rr] = vin[s][0];
+        stg[k * Gp + 2 * rr + 1] = vin[s][1];
+        if (kk != k) {
+          stg[kk * Gp + 2 * rr] = vin[s][2];
+          stg[kk * Gp + 2 * rr + 1] = vin[s][3];
+        }
+      }
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < Et; e += kThreads) {
+      int cr, j;
+      split(e, cr, j);
+      if (cr < cnt) t[at(cr, j)] = stg[e];
+    }
     __syncthreads();
   }
 }
 
 // ---------------------------------------------------------------------------
-// Row pass, inverse: read G rows of spectra transposed from t, inverse
+// Row pass, inverse: read G rows of spectra from t, inverse
 // transform along x, restrict to U -> z; partial r.z and r.z_old.
 // ---------------------------------------------------------------------------
 
@@ -1875,7 +2293,6 @@ __global__ void __launch_bounds__(kThreads, FAM == kFamCz ? 1 : 2)
   extern __shared__ __align__(16) unsigned char smem[];
   debug_fill_lds(smem);
   C* buf = (C*)smem;
-  R* stg = (R*)smem;
   C* twl = buf + twoff;
   int staged = -1;
   __shared__ double red[4];
@@ -1889,19 +2306,31 @@ __global__ void __launch_bounds__(kThreads, FAM == kFamCz ? 1 : 2)
     // ny: rows of the pass
     const int nx = SP ? sp_nodes(SP) : I.nx, ny = I.nrows, G = SP ? SP >> 8 : I.G,
               j0 = g * G;
-    BHX_GLOBAL const R* t = (BHX_GLOBAL const R*)I.t;
     // 1. issue together: `done` and the row group's unknown count (both
-    //    unchanged during the pass), the first kPre transposed loads of the
-    //    spectra (stg[k * G + jr] = t[k * ny + j0 + jr]) and the masks of
-    //    the output elements; then the output r (and z_old) values
+    //    unchanged during the pass), the first spectra pairs of the rows and
+    //    the masks of the output elements; then the output r (and z_old) values
     const int jn = min(G, ny - j0);
-    R tv[kPre];
+    const int rows = G >> 1;
+    const int bcx = SP ? SP & 3 : I.bcx;
+    const int np = plan_pairs(nx, bcx);
+    BHX_GLOBAL const R* t = (BHX_GLOBAL const R*)I.t + (size_t)j0 * nx;
+    // spectra of pair pidx = (packed row rr, k): both lines at k and its
+    // partner; the second line of the last group may not exist (0)
+    auto load_pair = [&](int pidx, R (&y)[4]) {
+      const int pc = min(pidx, rows * np - 1);
+      const int rr = pc / np, k = pc - rr * np;
+      const int kk = bcx == kDirichlet ? nx - 1 - k : (k == 0 ? 0 : nx - k);
+      const size_t oa = (size_t)min(2 * rr, jn - 1) * nx;
+      const size_t ob = (size_t)min(2 * rr + 1, jn - 1) * nx;
+      y[0] = t[oa + k];
+      y[1] = t[ob + k];
+      y[2] = t[oa + kk];
+      y[3] = t[ob + kk];
+    };
+    constexpr int kPP = 2;                     // pairs per thread loaded up front
+    R tv[kPP][4];
 #pragma unroll
-    for (int u = 0; u < kPre; ++u) {
-      const int e = min((int)threadIdx.x + u * kThreads, nx * G - 1);
-      const int k = e / G, jr = e - k * G;
-      tv[u] = t[(size_t)k * ny + j0 + min(jr, jn - 1)];
-    }
+    for (int u = 0; u < kPP; ++u) load_pair(threadIdx.x + u * kThreads, tv[u]);
     const int E = jn * nx;
     const size_t base = (size_t)j0 * nx;
     BHX_GLOBAL const uint8_t* __restrict__ mk = I.mask + base;
@@ -1938,59 +2367,21 @@ __global__ void __launch_bounds__(kThreads, FAM == kFamCz ? 1 : 2)
     XPlan<R, SP> X(B, I.planx);
     if constexpr (!CZ) X.cz = 0;   // chirp-z axes run on the CZ instances only
     X.stage(twl, I.planx, staged, false);
-    const int rows = G >> 1;
     const int st = X.stride();
-#pragma unroll
-    for (int u = 0; u < kPre; ++u) {
-      const int e = threadIdx.x + u * kThreads;
-      if (e < nx * G) stg[e] = (e % G) < jn ? tv[u] : (R)0;
-    }
-    for (int e = threadIdx.x + kPre * kThreads; e < nx * G; e += kThreads) {
-      const int k = e / G, jr = e - k * G;
-      stg[e] = jr < jn ? t[(size_t)k * ny + j0 + jr] : (R)0;
-    }
-    __syncthreads();
-    const int np = X.pairs();
     double acc = 0.0, acco = 0.0;
     if (X.cz) {
       // chirp-z DST-I (its own inverse): the first line of each pair, then
-      // the second, in the pair's row; outputs, z and dots per line.  The
-      // spectra share LDS with the rows: the first lines' ones go through
-      // registers before the rows are written, the second lines' are read
-      // again from t.
+      // the second, in the pair's row; outputs, z and dots per line
 #pragma unroll 1
       for (int h = 0; h < 2; ++h) {
-        R sv[kMaxPairs][2];
-#pragma unroll
-        for (int s = 0; s < kMaxPairs; ++s) {
-          const int pidx = threadIdx.x + s * kThreads;
-          if (pidx < rows * np) {
-            const int rr = pidx / np, k = pidx - rr * np;
-            const int kk = X.partner(k);
-            const int jr = 2 * rr + h;
-            if (h == 0) {
-              sv[s][0] = stg[k * G + jr];
-              sv[s][1] = stg[kk * G + jr];
-            } else {
-              sv[s][0] = jr < jn ? t[(size_t)k * ny + j0 + jr] : (R)0;
-              sv[s][1] = jr < jn ? t[(size_t)kk * ny + j0 + jr] : (R)0;
-            }
-          }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int s = 0; s < kMaxPairs; ++s) {
-          const int pidx = threadIdx.x + s * kThreads;
-          if (pidx < rows * np) {
-            const int rr = pidx / np, k = pidx - rr * np;
-            const int kk = X.partner(k);
-            X.put_cz(buf + rr * st, k, sv[s][0]);
-            if (kk != k) X.put_cz(buf + rr * st, kk, sv[s][1]);
-          }
+        for (int e = threadIdx.x; e < rows * nx; e += kThreads) {
+          const int rr = e / nx, k = e - rr * nx;
+          const int jr = 2 * rr + h;
+          X.put_cz(buf + rr * st, k, jr < jn ? t[(size_t)jr * nx + k] : (R)0);
         }
         X.zero_ends(buf, rows, st);
         __syncthreads();
-        dft_core<kWide>(X, buf, rows);
+        dft_core<kWide, true>(X, buf, rows);
         for (int e = threadIdx.x; e < E; e += kThreads) {
           const int jr = e / nx, i = e - jr * nx;
           if ((jr & 1) != h || !mk[e]) continue;
@@ -2004,30 +2395,29 @@ __global__ void __launch_bounds__(kThreads, FAM == kFamCz ? 1 : 2)
         __syncthreads();
       }
     } else {
-    // 2. inverse inputs of the pairs, through registers
-    C vin[kMaxPairs][2];
+    // 2. inverse inputs of the pairs into the packed rows
+    auto place = [&](int pidx, const R (&y)[4]) {
+      if (pidx >= rows * np) return;
+      const int rr = pidx / np, k = pidx - rr * np;
+      const int kk = X.partner(k);
+      const bool ha = 2 * rr < jn, hb = 2 * rr + 1 < jn;
+      C ink, inkk;
+      inv_pre_pair<R>(X, ha ? y[0] : (R)0, hb ? y[1] : (R)0, ha ? y[2] : (R)0,
+                      hb ? y[3] : (R)0, k, kk, ink, inkk);
+      X.put_pair(buf + rr * st, k, kk, ink, inkk);
+    };
 #pragma unroll
-    for (int s = 0; s < kMaxPairs; ++s) {
-      const int pidx = threadIdx.x + s * kThreads;
-      if (pidx < rows * np) {
-        const int rr = pidx / np, k = pidx - rr * np;
-        const int kk = X.partner(k);
-        inv_pre_pair<R>(X, stg[k * G + 2 * rr], stg[k * G + 2 * rr + 1], stg[kk * G + 2 * rr],
-                        stg[kk * G + 2 * rr + 1], k, kk, vin[s][0], vin[s][1]);
-      }
-    }
-    __syncthreads();
+    for (int u = 0; u < kPP; ++u) place(threadIdx.x + u * kThreads, tv[u]);
+    for (int p0 = threadIdx.x + kPP * kThreads; p0 < rows * np; p0 += kPP * kThreads) {
+      R y[kPP][4];
 #pragma unroll
-    for (int s = 0; s < kMaxPairs; ++s) {
-      const int pidx = threadIdx.x + s * kThreads;
-      if (pidx < rows * np) {
-        const int rr = pidx / np, k = pidx - rr * np;
-        X.put_pair(buf + rr * st, k, X.partner(k), vin[s][0], vin[s][1]);
-      }
+      for (int u = 0; u < kPP; ++u) load_pair(p0 + u * kThreads, y[u]);
+#pragma unroll
+      for (int u = 0; u < kPP; ++u) place(p0 + u * kThreads, y[u]);
     }
     X.zero_ends(buf, rows, st);
     __syncthreads();
-    dft_core<kWide>(X, buf, rows);
+    dft_core<kWide, true>(X, buf, rows);
     // 3. outputs: restrict, store z, dots
     auto emit = [&](int e, int m, double rv, double zo) {
       if (!m) return;
@@ -2561,7 +2951,7 @@ __global__ void __launch_bounds__(kThreads) k_finalize(const Batch* __restrict__
   }
 }
 
-// Plain CG counts its iterations here (the preconditioned path counts in k_col).
+// Plain CG counts its iterations here (the preconditioned path counts in the column solve).
 __global__ void k_bump(const Batch* __restrict__ Bp) {
   const Batch B = *(BHX_CONST const Batch*)Bp;   // scalar loads, kept in registers
   const int inst = blockIdx.x * blockDim.x + threadIdx.x;
@@ -2662,14 +3052,16 @@ hipError_t launch_setup(const Batch* B, int dim, int grid, hipStream_t st) {
 }
 // Launch on `st`; given events, through hipExtLaunchKernelGGL, whose dispatch
 // records them at kernel start and end.
-#define BHX_LAUNCH(kernel, grid, lds, st, e0, e1, ...)                                  \
+#define BHX_LAUNCH_T(kernel, threads, grid, lds, st, e0, e1, ...)                       \
   do {                                                                                \
     if ((e0) || (e1))                                                                 \
-      hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), lds, st, e0, e1, 0,   \
+      hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(threads), lds, st, e0, e1, 0,    \
                             __VA_ARGS__);                                             \
     else                                                                              \
-      hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), lds, st, __VA_ARGS__);   \
+      hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), lds, st, __VA_ARGS__);    \
   } while (0)
+#define BHX_LAUNCH(kernel, grid, lds, st, e0, e1, ...) \
+  BHX_LAUNCH_T(kernel, kThreads, grid, lds, st, e0, e1, __VA_ARGS__)
 
 template <int DIM>
 static hipError_t launch_stencil_dim(const Batch* B, int mode, int grid, int lpar,
@@ -2697,33 +3089,30 @@ hipError_t launch_resid(const Batch* B, int dim, int grid, hipStream_t st) {
 }
 // Compile-time shapes instantiated per pass family, as (G, L, bc): G lines
 // per work item, a 2^L-point core, Neumann (0), periodic (1) or Dirichlet (2).
-// Two dimensions: 64-2048 nodes (Neumann, periodic) and 63-2047 nodes with
-// n + 1 a power of two (Dirichlet), one packed row per item, FP64 and FP32
-// transforms; three dimensions (FP64): 128 and 256 nodes with the groups the
-// layout gives 128^3 and 256^3 (rows and y pencils 8, z pencils 16).
-#define BHX_COL2D_SHAPES(X)                                                             \
+// Two dimensions: rows of 64-2048 nodes (Neumann, periodic) and 63-2047 nodes
+// with n + 1 a power of two (Dirichlet), one packed row per item, FP64 and
+// FP32 transforms; three dimensions (FP64): 128 and 256 nodes with the groups
+// the layout gives 128^3 and 256^3 (rows 8, y pencils 16).
+#define BHX_ROW2D_SHAPES(X)                                                             \
   X(2, 6, 0) X(2, 6, 1) X(2, 7, 0) X(2, 7, 1) X(2, 8, 0) X(2, 8, 1) X(2, 9, 0) X(2, 9, 1) \
   X(2, 10, 0) X(2, 10, 1) X(2, 11, 0) X(2, 11, 1) X(2, 7, 2) X(2, 8, 2) X(2, 9, 2)         \
   X(2, 10, 2) X(2, 11, 2) X(2, 12, 2)
-#define BHX_ROW_SHAPES(X) BHX_COL2D_SHAPES(X) X(8, 7, 0) X(8, 7, 1) X(8, 8, 0) X(8, 8, 1)
-#define BHX_COLY_SHAPES(X) X(8, 7, 0) X(8, 7, 1) X(8, 8, 0) X(8, 8, 1)
-#define BHX_COLZ_SHAPES(X) X(16, 7, 0) X(16, 7, 1) X(16, 8, 0) X(16, 8, 1)
+#define BHX_ROW_SHAPES(X) BHX_ROW2D_SHAPES(X) X(8, 7, 0) X(8, 7, 1) X(8, 8, 0) X(8, 8, 1)
+#define BHX_Y_SHAPES(X) X(16, 7, 0) X(16, 7, 1) X(16, 8, 0) X(16, 8, 1)
 #define BHX_KEY(G, L, bc) (((G) << 8) | ((L) << 2) | (bc))
 
 // The environment variable BHX_SHAPE_KERNELS=0 keeps every launch on the
 // plan-table kernels (for comparing the two).
 int shape_key(int pass, int prec, int n, int m, int logm, int bluestein, int bc, int group) {
   if (bluestein || m != (bc == kDirichlet ? 2 * (n + 1) : n)) return 0;
-  if (prec != 0 && (group != 2 || (pass != kShapeRow && pass != kShapeCol2D))) return 0;
+  if (prec != 0 && (group != 2 || pass != kShapeRow)) return 0;
   if (logm < 1 || logm > 15 || group < 2 || group > 64) return 0;
   const int key = BHX_KEY(group, logm, bc);
   bool listed = false;
 #define BHX_IS(G, L, b) listed = listed || key == BHX_KEY(G, L, b);
   switch (pass) {
     case kShapeRow: BHX_ROW_SHAPES(BHX_IS) break;
-    case kShapeCol2D: BHX_COL2D_SHAPES(BHX_IS) break;
-    case kShapeColY: BHX_COLY_SHAPES(BHX_IS) break;
-    case kShapeColZ: BHX_COLZ_SHAPES(BHX_IS) break;
+    case kShapeY: BHX_Y_SHAPES(BHX_IS) break;
     default: break;
   }
 #undef BHX_IS
@@ -2733,10 +3122,8 @@ int shape_key(int pass, int prec, int n, int m, int logm, int bluestein, int bc,
   return key;
 }
 
-hipError_t launch_rowfwd(const Batch* B, int prec, int shape, int update, int stream_t, int grid,
-                         int lds, int twoff, int lpar, hipStream_t st, hipEvent_t e0,
-                         hipEvent_t e1) {
-  update |= stream_t ? 4 : 0;
+hipError_t launch_rowfwd(const Batch* B, int prec, int shape, int update, int grid, int lds,
+                         int twoff, int lpar, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
   if (prec != 0) {
     switch (shape) {
 #define BHX_CASE(G, L, bc)                                                             \
@@ -2744,7 +3131,7 @@ hipError_t launch_rowfwd(const Batch* B, int prec, int shape, int update, int st
     BHX_LAUNCH((k_rowfwd<float, BHX_KEY(G, L, bc)>), grid, lds, st, e0, e1, B, update, \
                twoff, lpar);                                                           \
     break;
-      BHX_COL2D_SHAPES(BHX_CASE)
+      BHX_ROW2D_SHAPES(BHX_CASE)
 #undef BHX_CASE
       case 0: BHX_LAUNCH((k_rowfwd<float, 0>), grid, lds, st, e0, e1, B, update, twoff, lpar); break;
       case kShapeWideKey:
@@ -2777,87 +3164,62 @@ hipError_t launch_rowfwd(const Batch* B, int prec, int shape, int update, int st
   return hipGetLastError();
 }
 template <typename R, int FAM>
-static hipError_t launch_col_fam(const Batch* B, int kind, int count_iter, int grid, int lds,
-                                 int twoff, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
-  switch (kind) {
-    case kCol2D: BHX_LAUNCH((k_col<R, kCol2D, 0, FAM>), grid, lds, st, e0, e1, B, count_iter, twoff); break;
-    case kColYFwd: BHX_LAUNCH((k_col<R, kColYFwd, 0, FAM>), grid, lds, st, e0, e1, B, count_iter, twoff); break;
-    case kColZ: BHX_LAUNCH((k_col<R, kColZ, 0, FAM>), grid, lds, st, e0, e1, B, count_iter, twoff); break;
-    case kColYInv: BHX_LAUNCH((k_col<R, kColYInv, 0, FAM>), grid, lds, st, e0, e1, B, count_iter, twoff); break;
+static hipError_t launch_ypass_fam(const Batch* B, int kind, int grid, int lds, int twoff,
+                                   hipStream_t st) {
+  if (kind == kColYFwd)
+    hipLaunchKernelGGL((k_ypass<R, kColYFwd, 0, FAM>), dim3(grid), dim3(kThreads), lds, st, B, twoff);
+  else
+    hipLaunchKernelGGL((k_ypass<R, kColYInv, 0, FAM>), dim3(grid), dim3(kThreads), lds, st, B, twoff);
+  return hipGetLastError();
+}
+hipError_t launch_ypass(const Batch* B, int prec, int shape, int kind, int grid, int lds,
+                        int twoff, hipStream_t st) {
+  if (shape == kShapeCzKey) return hipErrorInvalidValue;   // two dimensions only
+  if (plan_table_shape(shape)) {
+    const bool wide = shape == kShapeWideKey;
+    if (prec != 0)
+      return wide ? launch_ypass_fam<float, kFamWide>(B, kind, grid, lds, twoff, st)
+                  : launch_ypass_fam<float, kFamNarrow>(B, kind, grid, lds, twoff, st);
+    return wide ? launch_ypass_fam<double, kFamWide>(B, kind, grid, lds, twoff, st)
+                : launch_ypass_fam<double, kFamNarrow>(B, kind, grid, lds, twoff, st);
+  }
+  if (prec != 0) return hipErrorInvalidValue;
+  switch (shape) {
+#define BHX_CASE(G, L, bc)                                                                  \
+  case BHX_KEY(G, L, bc):                                                                   \
+    if (kind == kColYFwd)                                                                   \
+      hipLaunchKernelGGL((k_ypass<double, kColYFwd, BHX_KEY(G, L, bc)>), dim3(grid),        \
+                         dim3(kThreads), lds, st, B, twoff);                                \
+    else                                                                                    \
+      hipLaunchKernelGGL((k_ypass<double, kColYInv, BHX_KEY(G, L, bc)>), dim3(grid),        \
+                         dim3(kThreads), lds, st, B, twoff);                                \
+    break;
+    BHX_Y_SHAPES(BHX_CASE)
+#undef BHX_CASE
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
-template <typename R>
-static hipError_t launch_col_prec(const Batch* B, int kind, int shape, int count_iter, int grid,
-                                  int lds, int twoff, hipStream_t st, hipEvent_t e0,
-                                  hipEvent_t e1) {
-  if (shape == kShapeCzKey) {
-    // chirp-z Dirichlet axes exist in two dimensions only
-    if (kind != kCol2D) return hipErrorInvalidValue;
-    BHX_LAUNCH((k_col<R, kCol2D, 0, kFamCz>), grid, lds, st, e0, e1, B, count_iter, twoff);
-    return hipGetLastError();
-  }
-  return shape == kShapeWideKey
-             ? launch_col_fam<R, kFamWide>(B, kind, count_iter, grid, lds, twoff, st, e0, e1)
-             : launch_col_fam<R, kFamNarrow>(B, kind, count_iter, grid, lds, twoff, st, e0, e1);
+template <typename R, int PASS>
+static hipError_t launch_colsolve_pass(const Batch* B, int lng, int count_iter, int grid, int lds,
+                                       hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+  if (lng == 0)
+    BHX_LAUNCH_T((k_colsolve<R, PASS, 0>), kColThreads, grid, lds, st, e0, e1, B, count_iter);
+  else if (lng == 1 || sizeof(R) == 8)
+    BHX_LAUNCH_T((k_colsolve<R, PASS, 1>), kColThreads, grid, lds, st, e0, e1, B, count_iter);
+  else
+    BHX_LAUNCH_T((k_colsolve<float, PASS, 2>), kColThreads, grid, lds, st, e0, e1, B, count_iter);
+  return hipGetLastError();
 }
-hipError_t launch_col(const Batch* B, int prec, int shape, int kind, int count_iter, int grid,
-                      int lds, int twoff, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
-  if (shape == kShapeCzKey || shape == kShapeWideKey) {
-    return prec == 0
-               ? launch_col_prec<double>(B, kind, shape, count_iter, grid, lds, twoff, st, e0, e1)
-               : launch_col_prec<float>(B, kind, shape, count_iter, grid, lds, twoff, st, e0, e1);
-  }
-  if (shape != 0 && prec != 0) {
-    if (kind != kCol2D) return hipErrorInvalidValue;
-    switch (shape) {
-#define BHX_CASE_F(G, L, bc)                                                               \
-  case BHX_KEY(G, L, bc):                                                                  \
-    BHX_LAUNCH((k_col<float, kCol2D, BHX_KEY(G, L, bc)>), grid, lds, st, e0, e1, B,        \
-               count_iter, twoff);                                                         \
-    break;
-      BHX_COL2D_SHAPES(BHX_CASE_F)
-#undef BHX_CASE_F
-      default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-  }
-  if (shape != 0) {
-#define BHX_CASE_K(K, G, L, bc)                                                          \
-  case BHX_KEY(G, L, bc):                                                                \
-    BHX_LAUNCH((k_col<double, K, BHX_KEY(G, L, bc)>), grid, lds, st, e0, e1, B, count_iter, \
-               twoff);                                                                   \
-    break;
-#define BHX_CASE_2D(G, L, bc) BHX_CASE_K(kCol2D, G, L, bc)
-#define BHX_CASE_YF(G, L, bc) BHX_CASE_K(kColYFwd, G, L, bc)
-#define BHX_CASE_YI(G, L, bc) BHX_CASE_K(kColYInv, G, L, bc)
-#define BHX_CASE_Z(G, L, bc) BHX_CASE_K(kColZ, G, L, bc)
-    switch (kind) {
-      case kCol2D:
-        switch (shape) { BHX_COL2D_SHAPES(BHX_CASE_2D) default: return hipErrorInvalidValue; }
-        break;
-      case kColYFwd:
-        switch (shape) { BHX_COLY_SHAPES(BHX_CASE_YF) default: return hipErrorInvalidValue; }
-        break;
-      case kColYInv:
-        switch (shape) { BHX_COLY_SHAPES(BHX_CASE_YI) default: return hipErrorInvalidValue; }
-        break;
-      case kColZ:
-        switch (shape) { BHX_COLZ_SHAPES(BHX_CASE_Z) default: return hipErrorInvalidValue; }
-        break;
-      default: return hipErrorInvalidValue;
-    }
-#undef BHX_CASE_2D
-#undef BHX_CASE_YF
-#undef BHX_CASE_YI
-#undef BHX_CASE_Z
-#undef BHX_CASE_K
-    return hipGetLastError();
-  }
-  return prec == 0
-             ? launch_col_prec<double>(B, kind, 0, count_iter, grid, lds, twoff, st, e0, e1)
-             : launch_col_prec<float>(B, kind, 0, count_iter, grid, lds, twoff, st, e0, e1);
+hipError_t launch_colsolve(const Batch* B, int prec, int pass, int lng, int count_iter, int grid,
+                           int lds, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+  if (pass == kPassZ)
+    return prec != 0
+               ? launch_colsolve_pass<float, kPassZ>(B, lng, count_iter, grid, lds, st, e0, e1)
+               : launch_colsolve_pass<double, kPassZ>(B, lng, count_iter, grid, lds, st, e0, e1);
+  return prec != 0
+             ? launch_colsolve_pass<float, kPassC>(B, lng, count_iter, grid, lds, st, e0, e1)
+             : launch_colsolve_pass<double, kPassC>(B, lng, count_iter, grid, lds, st, e0, e1);
 }
 hipError_t launch_rowinv(const Batch* B, int prec, int shape, int grid, int lds, int twoff,
                          int lpar, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
@@ -2867,7 +3229,7 @@ hipError_t launch_rowinv(const Batch* B, int prec, int shape, int grid, int lds,
   case BHX_KEY(G, L, bc):                                                                 \
     BHX_LAUNCH((k_rowinv<float, BHX_KEY(G, L, bc)>), grid, lds, st, e0, e1, B, twoff, lpar); \
     break;
-      BHX_COL2D_SHAPES(BHX_CASE)
+      BHX_ROW2D_SHAPES(BHX_CASE)
 #undef BHX_CASE
       case 0: BHX_LAUNCH((k_rowinv<float, 0>), grid, lds, st, e0, e1, B, twoff, lpar); break;
       case kShapeWideKey:
@@ -2973,32 +3335,14 @@ hipError_t set_kernel_attributes() {
   };
   set((const void*)k_rowfwd<double, 0>);
   set((const void*)k_rowfwd<float, 0>);
-  set((const void*)k_col<double, kCol2D, 0>);
-  set((const void*)k_col<float, kCol2D, 0>);
-  set((const void*)k_col<double, kColYFwd, 0>);
-  set((const void*)k_col<float, kColYFwd, 0>);
-  set((const void*)k_col<double, kColZ, 0>);
-  set((const void*)k_col<float, kColZ, 0>);
-  set((const void*)k_col<double, kColYInv, 0>);
-  set((const void*)k_col<float, kColYInv, 0>);
   set((const void*)k_rowinv<double, 0>);
   set((const void*)k_rowinv<float, 0>);
   set((const void*)k_rowfwd<double, 0, kFamCz>);
   set((const void*)k_rowfwd<float, 0, kFamCz>);
-  set((const void*)k_col<double, kCol2D, 0, kFamCz>);
-  set((const void*)k_col<float, kCol2D, 0, kFamCz>);
   set((const void*)k_rowinv<double, 0, kFamCz>);
   set((const void*)k_rowinv<float, 0, kFamCz>);
   set((const void*)k_rowfwd<double, 0, kFamWide>);
   set((const void*)k_rowfwd<float, 0, kFamWide>);
-  set((const void*)k_col<double, kCol2D, 0, kFamWide>);
-  set((const void*)k_col<float, kCol2D, 0, kFamWide>);
-  set((const void*)k_col<double, kColYFwd, 0, kFamWide>);
-  set((const void*)k_col<float, kColYFwd, 0, kFamWide>);
-  set((const void*)k_col<double, kColZ, 0, kFamWide>);
-  set((const void*)k_col<float, kColZ, 0, kFamWide>);
-  set((const void*)k_col<double, kColYInv, 0, kFamWide>);
-  set((const void*)k_col<float, kColYInv, 0, kFamWide>);
   set((const void*)k_rowinv<double, 0, kFamWide>);
   set((const void*)k_rowinv<float, 0, kFamWide>);
   set((const void*)k_rowfwd_dense<double>);
@@ -3007,26 +3351,39 @@ hipError_t set_kernel_attributes() {
   set((const void*)k_col_dense<float>);
   set((const void*)k_rowinv_dense<double>);
   set((const void*)k_rowinv_dense<float>);
+  set((const void*)k_colsolve<double, kPassC, 0>);
+  set((const void*)k_colsolve<double, kPassC, 1>);
+  set((const void*)k_colsolve<float, kPassC, 0>);
+  set((const void*)k_colsolve<float, kPassC, 1>);
+  set((const void*)k_colsolve<float, kPassC, 2>);
+  set((const void*)k_colsolve<double, kPassZ, 0>);
+  set((const void*)k_colsolve<double, kPassZ, 1>);
+  set((const void*)k_colsolve<float, kPassZ, 0>);
+  set((const void*)k_colsolve<float, kPassZ, 1>);
+  set((const void*)k_colsolve<float, kPassZ, 2>);
+  set((const void*)k_ypass<double, kColYFwd, 0>);
+  set((const void*)k_ypass<float, kColYFwd, 0>);
+  set((const void*)k_ypass<double, kColYInv, 0>);
+  set((const void*)k_ypass<float, kColYInv, 0>);
+  set((const void*)k_ypass<double, kColYFwd, 0, kFamWide>);
+  set((const void*)k_ypass<float, kColYFwd, 0, kFamWide>);
+  set((const void*)k_ypass<double, kColYInv, 0, kFamWide>);
+  set((const void*)k_ypass<float, kColYInv, 0, kFamWide>);
 #define BHX_SET_ROW(G, L, bc)                                        \
   set((const void*)k_rowfwd<double, BHX_KEY(G, L, bc)>);             \
   set((const void*)k_rowinv<double, BHX_KEY(G, L, bc)>);
 #define BHX_SET_2D(G, L, bc)                                         \
-  set((const void*)k_col<double, kCol2D, BHX_KEY(G, L, bc)>);        \
-  set((const void*)k_col<float, kCol2D, BHX_KEY(G, L, bc)>);         \
   set((const void*)k_rowfwd<float, BHX_KEY(G, L, bc)>);              \
   set((const void*)k_rowinv<float, BHX_KEY(G, L, bc)>);
 #define BHX_SET_Y(G, L, bc)                                          \
-  set((const void*)k_col<double, kColYFwd, BHX_KEY(G, L, bc)>);      \
-  set((const void*)k_col<double, kColYInv, BHX_KEY(G, L, bc)>);
-#define BHX_SET_Z(G, L, bc) set((const void*)k_col<double, kColZ, BHX_KEY(G, L, bc)>);
+  set((const void*)k_ypass<double, kColYFwd, BHX_KEY(G, L, bc)>);    \
+  set((const void*)k_ypass<double, kColYInv, BHX_KEY(G, L, bc)>);
   BHX_ROW_SHAPES(BHX_SET_ROW)
-  BHX_COL2D_SHAPES(BHX_SET_2D)
-  BHX_COLY_SHAPES(BHX_SET_Y)
-  BHX_COLZ_SHAPES(BHX_SET_Z)
+  BHX_ROW2D_SHAPES(BHX_SET_2D)
+  BHX_Y_SHAPES(BHX_SET_Y)
 #undef BHX_SET_ROW
 #undef BHX_SET_2D
 #undef BHX_SET_Y
-#undef BHX_SET_Z
   return e;
 }
 

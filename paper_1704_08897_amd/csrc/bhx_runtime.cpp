@@ -109,6 +109,10 @@ bool length_supported(int n, int bc, int prec) {
   return true;
 }
 
+int col_lds(int n, int W, int prec) {
+  return W * col_stride(n, col_rows(n, W), W) * (prec == 0 ? 8 : 4);
+}
+
 bool make_layout(int nx, int ny, int nz, int prec, int mx, int my, int mz, int rows_user,
                  Layout* L, bool dense) {
   const bool d3 = mz > 0;
@@ -128,22 +132,29 @@ bool make_layout(int nx, int ny, int nz, int prec, int mx, int my, int mz, int r
   };
   const long nrows = (long)ny * nz;                      // x rows
   const int rx = rows_for(nx, mx, nrows, rows_cap);
-  const int ry = rows_for(ny, my, (long)nx * nz, rows_cap);
-  // z pencils are strided: wider groups give longer contiguous runs
+  // y pencils are strided: wider groups give longer contiguous runs
+  const int ry = rows_for(ny, my, (long)nx * nz, d3 ? kMaxGc / 2 : rows_cap);
   const int rz = d3 ? rows_for(nz, mz, (long)nx * ny, kMaxGc / 2) : 1;
   if (rx < 1 || ry < 1 || rz < 1) return false;
+  // columns per item of the column solve: the wide items' 16 lanes per column
+  // take fewer steps per row and longer runs of memory, the others' 64 lanes
+  // fill the GPU from fewer columns and take longer axes
+  auto width = [&](int n, long cols) {
+    return n <= kColWideMax && (rows_user < 0 || cols >= kColWideMin) ? kColWide : kColWaves;
+  };
   L->G = dense ? kDenseG : 2 * rx;
-  L->Gc = dense ? kDenseG : 2 * ry;
-  L->Gz = d3 ? 2 * rz : 0;
-  if (L->Gc > kMaxGc || L->Gz > kMaxGc) return false;
+  L->Gc = dense ? kDenseG : d3 ? 2 * ry : width(ny, nx);
+  L->Gz = d3 ? width(nz, (long)nx * ny) : 0;
+  if (d3 && (L->Gc > kMaxGc || (long)nx * ((ny + 2 * rz - 1) / (2 * rz)) > kItemMask)) return false;
   const int tx = d3 ? kTileX3 : kTileX, ty = d3 ? kTileY3 : kTileY, tz = d3 ? kTileZ3 : 1;
   L->tiles_x = (nx + tx - 1) / tx;
   L->tiles_y = (ny + ty - 1) / ty;
   L->tiles_z = (nz + tz - 1) / tz;
+  const long ncg = (nx + L->Gc - 1) / L->Gc;
   const long items[kNumPass] = {(long)L->tiles_x * L->tiles_y * L->tiles_z,
                                 (nrows + L->G - 1) / L->G,
-                                ((long)nx * nz + L->Gc - 1) / L->Gc,
-                                d3 ? (long)nx * ((ny + L->Gz - 1) / L->Gz) : 0, 0, 0};
+                                d3 ? nz * ncg : ncg,
+                                d3 ? ((long)nx * ny + L->Gz - 1) / L->Gz : 0, 0, 0};
   for (int p = 0; p < kNumPass; ++p) {
     if (items[p] > kItemMask) return false;
     L->n_items[p] = (int)items[p];
@@ -482,24 +493,23 @@ namespace {
 
 }  // namespace
 
-// The column-transform launches of one preconditioner application: one in
-// two dimensions; y forward, z (with the scale) and y inverse in three.
-// Given events, they time the whole group (in three dimensions, recorded on
-// the stream around the three launches).
+// The column launches of one preconditioner application: the column solve
+// along y in two dimensions; y forward, the solve along z and y inverse in
+// three.  Given events, they time the whole group (in three dimensions,
+// recorded on the stream around the three launches).
 hipError_t launch_columns(const Batch* B, const Resolved& R, const Grids& g, int count_iter,
                           hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
   if (g.dim == 2)
-    return launch_col(B, R.precision, g.shape_c, kCol2D, count_iter, g.c, g.lds_c, g.tw_c, st,
-                      e0, e1);
+    return launch_colsolve(B, R.precision, kPassC, g.lng, count_iter, g.c, g.lds_c, st, e0, e1);
   hipError_t e;
   if (e0 && (e = hipEventRecord(e0, st)) != hipSuccess) return e;
-  if ((e = launch_col(B, R.precision, g.shape_c, kColYFwd, 0, g.c, g.lds_c, g.tw_c, st)) !=
+  if ((e = launch_ypass(B, R.precision, g.shape_c, kColYFwd, g.c, g.lds_c, g.tw_c, st)) !=
       hipSuccess)
     return e;
-  if ((e = launch_col(B, R.precision, g.shape_z, kColZ, count_iter, g.z, g.lds_z, g.tw_z, st)) !=
+  if ((e = launch_colsolve(B, R.precision, kPassZ, g.lng, count_iter, g.z, g.lds_z, st)) !=
       hipSuccess)
     return e;
-  if ((e = launch_col(B, R.precision, g.shape_c, kColYInv, 0, g.c, g.lds_c, g.tw_c, st)) !=
+  if ((e = launch_ypass(B, R.precision, g.shape_c, kColYInv, g.c, g.lds_c, g.tw_c, st)) !=
       hipSuccess)
     return e;
   if (e1) return hipEventRecord(e1, st);
@@ -520,8 +530,8 @@ static hipError_t launch_rowpass_fwd(const Batch* B, const Resolved& R, const Gr
                                      int update, int lpar, hipStream_t st, hipEvent_t e0,
                                      hipEvent_t e1) {
   hipError_t e;
-  if (g.fft && (e = launch_rowfwd(B, R.precision, g.shape_r, update, g.stream_t, g.r, g.lds_r,
-                                  g.tw_r, lpar, st, e0, g.dense ? nullptr : e1)) != hipSuccess)
+  if (g.fft && (e = launch_rowfwd(B, R.precision, g.shape_r, update, g.r, g.lds_r, g.tw_r, lpar,
+                                  st, e0, g.dense ? nullptr : e1)) != hipSuccess)
     return e;
   if (g.dense && (e = launch_rowfwd_dense(B, R.precision, update, g.rd, g.lds_rd, g.tab_rd, lpar,
                                           st, g.fft ? nullptr : e0, e1)) != hipSuccess)
@@ -593,7 +603,7 @@ hipError_t launch_iterations(const Batch* B, int n_inst, const Resolved& R, cons
       BHX_TRY(launch_rowpass_inv(B, R, g, par, st, e0(3, c), e1(3, c)));
     } else {
       // plain CG: update-only row pass, iteration count, z = r
-      BHX_TRY(launch_rowfwd(B, R.precision, g.shape_r, 2, g.stream_t, g.r, g.lds_r, g.tw_r, par, st,
+      BHX_TRY(launch_rowfwd(B, R.precision, g.shape_r, 2, g.r, g.lds_r, g.tw_r, par, st,
                             e0(1, c), e1(1, c)));
       BHX_TRY(maybe_reduce(B, g, kRedRR, par, st));
       BHX_TRY(launch_bump(B, n_inst, st));
@@ -637,9 +647,8 @@ hipError_t run_chunk(bhx_handle* hd, const Batch* B, int n_inst, const Resolved&
         gr.prec == R.precision && gr.chunk == R.chunk &&
         gr.precond == R.precond && gr.gs == g.s && gr.gr == g.r && gr.gc == g.c &&
         gr.lds_r == g.lds_r && gr.tw_r == g.tw_r && gr.lds_c == g.lds_c && gr.tw_c == g.tw_c &&
-        gr.dim == g.dim && gr.gz == g.z && gr.lds_z == g.lds_z && gr.tw_z == g.tw_z &&
-        gr.shape_r == g.shape_r && gr.shape_c == g.shape_c && gr.shape_z == g.shape_z &&
-        gr.stream_t == g.stream_t && gr.fft == g.fft && gr.dense == g.dense &&
+        gr.dim == g.dim && gr.gz == g.z && gr.lds_z == g.lds_z && gr.lng == g.lng &&
+        gr.shape_r == g.shape_r && gr.shape_c == g.shape_c && gr.fft == g.fft && gr.dense == g.dense &&
         gr.rd == g.rd && gr.cd == g.cd && gr.lds_rd == g.lds_rd && gr.tab_rd == g.tab_rd &&
         gr.lds_cd == g.lds_cd && gr.tab_cd == g.tab_cd &&
         gr.profile == R.profile && (gr.exec != nullptr) == graph) {
@@ -654,9 +663,8 @@ hipError_t run_chunk(bhx_handle* hd, const Batch* B, int n_inst, const Resolved&
   G.reduce = g.reduce;
   G.gs = g.s; G.gr = g.r; G.gc = g.c; G.profile = R.profile;
   G.lds_r = g.lds_r; G.tw_r = g.tw_r; G.lds_c = g.lds_c; G.tw_c = g.tw_c;
-  G.dim = g.dim; G.gz = g.z; G.lds_z = g.lds_z; G.tw_z = g.tw_z;
-  G.shape_r = g.shape_r; G.shape_c = g.shape_c; G.shape_z = g.shape_z;
-  G.stream_t = g.stream_t;
+  G.dim = g.dim; G.gz = g.z; G.lds_z = g.lds_z; G.lng = g.lng;
+  G.shape_r = g.shape_r; G.shape_c = g.shape_c;
   G.fft = g.fft; G.dense = g.dense; G.rd = g.rd; G.cd = g.cd;
   G.lds_rd = g.lds_rd; G.tab_rd = g.tab_rd; G.lds_cd = g.lds_cd; G.tab_cd = g.tab_cd;
   hipError_t e;
@@ -783,6 +791,8 @@ void describe_batch(const PlanCache& plans, int n, const InstSpec* specs, const 
     I.nx = S.nx; I.ny = S.ny; I.nz = nz; I.nrows = S.ny * nz;
     I.bcx = S.bcx; I.bcy = S.bcy; I.bcz = dim == 3 ? S.bcz : 0;
     I.planx = D->px[i]; I.plany = D->py[i]; I.planz = D->pz[i];
+    I.lamx = plans.plan(I.planx).off_lam;
+    I.lamy = plans.plan(I.plany).off_lam;
     I.G = L.G; I.Gc = L.Gc; I.Gz = L.Gz;
     I.tiles_x = L.tiles_x; I.tiles_y = L.tiles_y; I.tiles_z = L.tiles_z;
     for (int p = 0; p < kNumPass; ++p) I.n_items[p] = L.n_items[p];
@@ -848,41 +858,46 @@ int batch_grids(const PlanCache& plans, const BatchDesc& D, const Resolved& R, i
                 Grids* gout) {
   const int n = (int)D.inst.size();
   const int dim = D.dim;
-  Grids g;
+  Grids g{};
   g.dim = dim;
   g.count = n;
   for (int i = 0; i < n; ++i) g.reduce |= D.inst[i].reduce;
   const int ni[kNumPass] = {(int)D.items[kPassS].size(), (int)D.items[kPassR].size(),
                             (int)D.items[kPassC].size(), (int)D.items[kPassZ].size()};
-  g.s = std::max(1, std::min(ni[kPassS], num_cu * R.sched.occ_s));
-  g.r = std::max(1, std::min(ni[kPassR], num_cu * R.sched.occ_r));
-  g.c = std::max(1, std::min(ni[kPassC], num_cu * R.sched.occ_c));
-  g.z = dim == 3 ? std::max(1, std::min(ni[kPassZ], num_cu * R.sched.occ_c)) : 0;
+  // whole multiples of the eight XCDs, so that logical_block() keeps
+  // neighbouring items, which share lines of memory, on one of them
+  auto grid = [&](int items, int occ) {
+    return std::max(8, std::min((items + 7) / 8 * 8, num_cu * occ));
+  };
+  g.s = grid(ni[kPassS], R.sched.occ_s);
+  g.r = grid(ni[kPassR], R.sched.occ_r);
+  g.c = grid(ni[kPassC], R.sched.occ_c);
+  g.z = dim == 3 ? grid(ni[kPassZ], R.sched.occ_c) : 0;
   {
     // dynamic LDS: packed rows followed by the staged plan tables
     const int csize = R.precision == 0 ? 16 : 8;
-    int buf_r = 0, tab_r = 0, buf_c = 0, tab_c = 0, buf_z = 0, tab_z = 0;
+    int buf_r = 0, tab_r = 0, buf_c = 0, tab_c = 0;
     for (int i = 0; i < n; ++i) {
       if (D.dense[i]) continue;                 // no FFT pass works on it
       const AxisPlan& PX = plans.plan(D.px[i]);
-      const AxisPlan& PY = plans.plan(D.py[i]);
       buf_r = std::max(buf_r, (D.lay[i].G / 2) * row_slots(PX.m));
       tab_r = std::max(tab_r, table_slots(PX.n, PX.m, PX.bc, false));
-      buf_c = std::max(buf_c, (D.lay[i].Gc / 2) * row_slots(PY.m));
-      tab_c = std::max(tab_c, table_slots(PY.n, PY.m, PY.bc, dim == 2));
       if (dim == 3) {
-        const AxisPlan& PZ = plans.plan(D.pz[i]);
-        buf_z = std::max(buf_z, (D.lay[i].Gz / 2) * row_slots(PZ.m));
-        tab_z = std::max(tab_z, table_slots(PZ.n, PZ.m, PZ.bc, true));
+        const AxisPlan& PY = plans.plan(D.py[i]);
+        buf_c = std::max(buf_c, (D.lay[i].Gc / 2) * row_slots(PY.m));
+        tab_c = std::max(tab_c, table_slots(PY.n, PY.m, PY.bc, false));
+        g.lds_z = std::max(g.lds_z, col_lds(D.inst[i].nz, D.lay[i].Gz, R.precision));
+        g.lng = std::max(g.lng, col_class(D.inst[i].nz, D.lay[i].Gz));
+      } else {
+        g.lds_c = std::max(g.lds_c, col_lds(D.inst[i].ny, D.lay[i].Gc, R.precision));
+        g.lng = std::max(g.lng, col_class(D.inst[i].ny, D.lay[i].Gc));
       }
     }
     g.tw_r = buf_r;
     g.lds_r = (buf_r + tab_r) * csize;
     g.tw_c = buf_c;
-    g.lds_c = (buf_c + tab_c) * csize;
-    g.tw_z = buf_z;
-    g.lds_z = (buf_z + tab_z) * csize;
-    if (g.lds_r > kLdsDynMax || g.lds_c > kLdsDynMax || g.lds_z > kLdsDynMax) return BHX_ERR_ARG;
+    if (dim == 3) g.lds_c = (buf_c + tab_c) * csize;
+    if (g.lds_r > kLdsDynMax || g.lds_c > kLdsDynMax) return BHX_ERR_ARG;
   }
   int f0 = -1;                                  // first FFT-family instance
   for (int i = 0; i < n && f0 < 0; ++i)
@@ -895,12 +910,10 @@ int batch_grids(const PlanCache& plans, const BatchDesc& D, const Resolved& R, i
       return shape_key(pass, R.precision, P.n, P.m, P.logm, P.bluestein, P.bc, group);
     };
     g.shape_r = key(kShapeRow, plans.plan(D.px[f0]), D.lay[f0].G);
-    g.shape_c = key(dim == 3 ? kShapeColY : kShapeCol2D, plans.plan(D.py[f0]), D.lay[f0].Gc);
-    g.shape_z = dim == 3 ? key(kShapeColZ, plans.plan(D.pz[f0]), D.lay[f0].Gz) : 0;
+    g.shape_c = dim == 3 ? key(kShapeY, plans.plan(D.py[f0]), D.lay[f0].Gc) : 0;
     for (int i = f0 + 1; i < n; ++i) {
       if (D.dense[i]) continue;
       if (D.px[i] != D.px[f0] || D.lay[i].G != D.lay[f0].G) g.shape_r = 0;
-      if (D.pz[i] != D.pz[f0] || D.lay[i].Gz != D.lay[f0].Gz) g.shape_z = 0;
       if (D.py[i] != D.py[f0] || D.lay[i].Gc != D.lay[f0].Gc) g.shape_c = 0;
     }
     // plan-table launches: the kernel family from the longest work item
@@ -912,8 +925,7 @@ int batch_grids(const PlanCache& plans, const BatchDesc& D, const Resolved& R, i
     // is the packed rows alone
     const int csize = R.precision == 0 ? 16 : 8;
     if (plan_table_shape(g.shape_r)) g.lds_r = g.tw_r * csize;
-    if (plan_table_shape(g.shape_c)) g.lds_c = g.tw_c * csize;
-    if (dim == 3 && plan_table_shape(g.shape_z)) g.lds_z = g.tw_z * csize;
+    if (dim == 3 && plan_table_shape(g.shape_c)) g.lds_c = g.tw_c * csize;
   }
   {
     int nxm = 0, nym = 0;
@@ -926,14 +938,6 @@ int batch_grids(const PlanCache& plans, const BatchDesc& D, const Resolved& R, i
     if (g.dense)
       dense_grids(R.precision, nxm, nym, (int)D.items[kPassRD].size(),
                   (int)D.items[kPassCD].size(), num_cu, R.sched.occ_d, &g);
-  }
-  {
-    // non-temporal stores of t in the row-forward pass while the launch's t
-    // arrays are small (1024^2 FP64: 12.5 -> 11.8 us per launch; 2048^2:
-    // 46 -> 91 us, so never for large t)
-    size_t tb = 0;
-    for (int i = 0; i < n; ++i) tb += D.lay[i].off_part - D.lay[i].off_t;
-    g.stream_t = tb <= kStreamTMax;
   }
   *gout = g;
   return BHX_OK;
@@ -948,12 +952,11 @@ void plan_family(const AxisPlan& P, int rows, int* shape) {
 }
 
 void plan_families(const PlanCache& plans, const BatchDesc& D, Grids* g) {
-  const bool sr = g->shape_r == 0, sc = g->shape_c == 0, sz = g->shape_z == 0;
+  const bool sr = g->shape_r == 0, sc = D.dim == 3 && g->shape_c == 0;
   for (size_t i = 0; i < D.inst.size(); ++i) {
     if (D.dense[i]) continue;
     if (sr) plan_family(plans.plan(D.px[i]), D.lay[i].G / 2, &g->shape_r);
     if (sc) plan_family(plans.plan(D.py[i]), D.lay[i].Gc / 2, &g->shape_c);
-    if (sz && D.dim == 3) plan_family(plans.plan(D.pz[i]), D.lay[i].Gz / 2, &g->shape_z);
   }
 }
 

@@ -67,7 +67,9 @@ struct Layout {
 };
 
 // Choose row-group sizes and item counts; false if the size is unsupported.
-// mz = 0: two dimensions (nz = 1); otherwise the z core length.
+// mz = 0: two dimensions (nz = 1); otherwise the z core length (the column
+// solve along the last axis needs no transform, but takes the lengths that
+// have one).
 // dense: the instance's preconditioner runs the dense-transform passes
 // (row and column groups of kDenseG lines).
 // rows_cap: packed rows per transform work item; 0 = the built-in policy
@@ -79,6 +81,8 @@ inline bool make_layout(int nx, int ny, int prec, int mx, int my, int rows_cap, 
                         bool dense = false) {
   return make_layout(nx, ny, 1, prec, mx, my, 0, rows_cap, L, dense);
 }
+// Dynamic LDS of the column solve for an axis of n nodes, W columns per item.
+int col_lds(int n, int W, int prec);
 // Core FFT length of a transform of length n (power of two, or Bluestein).
 int core_length(int n);
 // Spacing of the float64 workspace vectors (elements), 256-byte aligned.
@@ -109,13 +113,13 @@ Resolved resolve_opts(const bhx_opts* o);
 struct Grids {
   int s, r, c;             // persistent grid sizes of the stencil, row and column passes
   int lds_r, tw_r;         // row passes: dynamic LDS bytes, twiddle offset (complex elements)
-  int lds_c, tw_c;         // column (y) passes
-  int dim = 2;             // 3: column passes along y, z, y
-  int z = 0, lds_z = 0, tw_z = 0;   // z pass (three dimensions)
+  int lds_c, tw_c;         // column solve (two dimensions) or y transforms (three)
+  int dim = 2;             // 3: y transform, column solve along z, y transform
+  int z = 0, lds_z = 0;    // column solve along z (three dimensions)
+  int lng = 0;             // column solve: the largest col_class
   int count = 0;           // instances of the batch
   int reduce = 0;          // 1: some instance has Inst::reduce (k_reduce launches)
-  int shape_r = 0, shape_c = 0, shape_z = 0;   // compile-time shapes of the passes (shape_key)
-  int stream_t = 0;        // 1: the row-forward pass stores t non-temporally
+  int shape_r = 0, shape_c = 0;   // compile-time shapes of the passes (shape_key)
   int fft = 1, dense = 0;  // launch the FFT-family / dense-transform passes
   int rd = 0, cd = 0;      // persistent grids of the dense row and column passes
   int lds_rd = 0, tab_rd = 0, lds_cd = 0, tab_cd = 0;   // their LDS and table offsets
@@ -138,7 +142,7 @@ struct BatchDesc {
 // kShapeCzKey): raised to what an axis plan with `rows` packed rows per work
 // item needs; compile-time shapes are left alone.
 void plan_family(const AxisPlan& P, int rows, int* shape);
-// The same over every FFT-family instance of a batch, for the three passes.
+// The same over every FFT-family instance of a batch, for the row and y passes.
 void plan_families(const PlanCache& plans, const BatchDesc& D, Grids* g);
 
 // Where the driver loop finds a prepared batch's device state.
@@ -153,10 +157,6 @@ struct DriveCtx {
                               // the work lists (needs the handle's host copies)
 };
 
-// Largest total of a launch's t arrays (bytes) whose row-forward stores go
-// non-temporal: one 1024 x 1024 FP64 instance.
-constexpr size_t kStreamTMax = (size_t)8 << 20;
-
 struct Graph {
   hipGraphExec_t exec = nullptr;
   hipStream_t stream = nullptr;
@@ -164,8 +164,7 @@ struct Graph {
   int count = 0;
   int prec = -1, chunk = 0, precond = -1, gs = 0, gr = 0, gc = 0, profile = 0;
   int lds_r = 0, tw_r = 0, lds_c = 0, tw_c = 0;
-  int dim = 2, gz = 0, lds_z = 0, tw_z = 0, reduce = 0, shape_r = 0, shape_c = 0, shape_z = 0;
-  int stream_t = 0;
+  int dim = 2, gz = 0, lds_z = 0, lng = 0, reduce = 0, shape_r = 0, shape_c = 0;
   int fft = 1, dense = 0, rd = 0, cd = 0, lds_rd = 0, tab_rd = 0, lds_cd = 0, tab_cd = 0;
   std::vector<hipEvent_t> ev;   // [pass][iteration][start, end] when profiling
 };
