@@ -744,8 +744,8 @@ struct InstPtrs {
 };
 InstPtrs instance0(bhx_handle* hd, const InstSpec& S, const Resolved& R) {
   Layout L;
-  make_layout(S.nx, S.ny, R.precision, core_length(fft_length(S.nx, S.bcx)),
-              core_length(fft_length(S.ny, S.bcy)), R.sched.rows_cap, &L);
+  make_layout(S.nx, S.ny, R.precision, core_length(S.nx, S.bcx),
+              core_length(S.ny, S.bcy), R.sched.rows_cap, &L);
   char* base = (char*)hd->ws + align256(sizeof(Ctl));
   return {(uint8_t*)(base + L.off_mask), (double*)(base + L.off_vec), (Ctl*)hd->ws};
 }

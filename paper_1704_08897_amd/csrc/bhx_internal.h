@@ -153,7 +153,8 @@ enum Done { kRunning = 0, kConverged = 1, kMaxIt = 2, kBreakdown = 3, kSkip = 4 
 struct AxisPlan {
   int n;
   int bc;          // Bc
-  int m;           // power-of-two core length (== nf, or >= 2nf-1 for Bluestein)
+  int m;           // power-of-two core length (== nf, or for Bluestein >= 2nf-1,
+                   // >= 3n for a DST-I through its odd extension)
   int logm;
   int bluestein;   // 0: direct radix-4/2 core; 1: chirp-z through length m
   int off_tw;      // W_m^k = exp(-2 pi i k / m), k < m/2        (complex table)
@@ -166,7 +167,7 @@ struct AxisPlan {
                    // points for the chirp-z DST-I (cz)
   int cz;          // 1: DST-I as a chirp-z transform: x at 1..n of a DFT of length
                    // 2(n+1) (chirp exp(-i pi k^2 / (2 nf))), outputs 0..n, one real
-                   // line per complex row (Dirichlet axes of 1024-2046 nodes)
+                   // line per complex row (Dirichlet axes of 1366-2046 nodes)
   // Dense form of the 1-D transform (n <= kDenseMax, else dense_P = 0): the
   // unnormalised basis T(k, i) = dtab[f(((k + ck) (di i + ci)) mod P)] with
   // (ck, di, ci, P) = (0, 2, 1, 4n) and dtab[a] = cos(pi a / 2n) (DCT-II),

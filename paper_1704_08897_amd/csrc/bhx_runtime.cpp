@@ -76,11 +76,25 @@ void free_graph(Graph& G) {
 
 size_t vec_stride(int nx, int ny) { return align_up((size_t)nx * ny, 32); }
 
-int core_length(int n) {
-  if (is_pow2(n)) return n;
+// Smallest power of two that is at least n.
+static int pow2_at_least(int n) {
   int m = 1;
-  while (m < 2 * n - 1) m <<= 1;
+  while (m < n) m <<= 1;
   return m;
+}
+
+// A Bluestein core computes sum_j x_j b(k - j) as a cyclic convolution, whose
+// length has to keep apart the lags k - j that the outputs in use meet.  A DFT
+// of length nf with every output in use meets 2 nf - 1.  The odd extension of
+// a DST-I is zero at 0 and n + 1 and only its bins 1..n are read: lags -2n to
+// n - 1, 3n of them instead of 4n + 3.  Four in ten lengths get by with half
+// the core: 600 nodes with 2048 points (was 4096).  1024 to 1365 nodes take
+// both lines of a row at once in 4096 points, where the chirp-z form runs the
+// core once per line: a 1100x600 solve went from 204 to 145 ms.
+int core_length(int n, int bc) {
+  const int nf = fft_length(n, bc);
+  if (is_pow2(nf)) return nf;
+  return pow2_at_least(bc == kDirichlet && !dst_chirp(n, bc) ? 3 * n : 2 * nf - 1);
 }
 
 // Complex slots of one packed FFT row in LDS, pad slots included (the
@@ -89,11 +103,13 @@ int row_slots(int m) { return rpos_code(m, rpos_shift(ilog2(m))); }
 
 
 // Length of the DFT behind the 1-D transform of an axis of n nodes.
-// A Dirichlet axis of 1024 to 2046 nodes, whose odd extension of 2(n + 1)
+// A Dirichlet axis of 1366 to 2046 nodes, whose odd extension of 2(n + 1)
 // points would need an 8192-point Bluestein core (no room in LDS in FP64),
 // takes its DST-I as a chirp-z transform of n + 1 points instead: the DFT of
 // length 2(n + 1) of x placed at 1..n, evaluated at 0..n (dst_chirp).
-bool dst_chirp(int n, int bc) { return bc == kDirichlet && n >= 1024 && n <= 2046; }
+bool dst_chirp(int n, int bc) { return bc == kDirichlet && 3 * n > 4096 && n <= 2046; }
+// Dirichlet axes that the y and z directions of three dimensions do not take.
+bool dst_long(int n, int bc) { return bc == kDirichlet && n >= 1024 && n <= 2046; }
 int fft_length(int n, int bc) {
   if (bc != kDirichlet) return n;
   return dst_chirp(n, bc) ? n + 1 : 2 * (n + 1);
@@ -102,7 +118,10 @@ int fft_length(int n, int bc) {
 bool length_supported(int n, int bc, int prec) {
   if (n < 4) return false;
   const int csize = prec == 0 ? 16 : 8;
-  const int m = core_length(fft_length(n, bc));
+  // The range is that of the full convolution (2 nf - 1 points; n + 1 point
+  // chirp-z from 1024 nodes on), whose core is never shorter than core_length.
+  const int nf = bc != kDirichlet ? n : dst_long(n, bc) ? n + 1 : 2 * (n + 1);
+  const int m = is_pow2(nf) ? nf : pow2_at_least(2 * nf - 1);
   if ((long)row_slots(m) * csize > kLdsBytes) return false;        // one packed row must fit
   if ((long)(row_slots(m) + table_slots(n, m, bc, true)) * csize > kLdsDynMax) return false;
   if ((n / 2 + 1) > kThreads * kMaxPairs) return false;
@@ -175,8 +194,8 @@ bool make_layout(int nx, int ny, int nz, int prec, int mx, int my, int mz, int r
 size_t instance_bytes(int nx, int ny, int bcx, int bcy, int prec, int rows_user) {
   Layout L;
   if (!length_supported(nx, bcx, prec) || !length_supported(ny, bcy, prec)) return 0;
-  if (!make_layout(nx, ny, prec, core_length(fft_length(nx, bcx)),
-                   core_length(fft_length(ny, bcy)), rows_user, &L))
+  if (!make_layout(nx, ny, prec, core_length(nx, bcx),
+                   core_length(ny, bcy), rows_user, &L))
     return 0;
   return L.bytes;
 }
@@ -187,9 +206,9 @@ size_t instance_bytes3(int nx, int ny, int nz, int bcx, int bcy, int bcz, int pr
       !length_supported(nz, bcz, prec))
     return 0;
   // the three-dimensional column passes have no chirp-z DST-I
-  if (dst_chirp(ny, bcy) || dst_chirp(nz, bcz)) return 0;
-  if (!make_layout(nx, ny, nz, prec, core_length(fft_length(nx, bcx)),
-                   core_length(fft_length(ny, bcy)), core_length(fft_length(nz, bcz)), 0, &L))
+  if (dst_long(ny, bcy) || dst_long(nz, bcz)) return 0;
+  if (!make_layout(nx, ny, nz, prec, core_length(nx, bcx),
+                   core_length(ny, bcy), core_length(nz, bcz), 0, &L))
     return 0;
   return L.bytes;
 }
@@ -249,7 +268,7 @@ int PlanCache::get(int n, int bc) {
   P.nf = fft_length(n, bc);
   const int nf = P.nf;
   P.cz = dst_chirp(n, bc);
-  P.m = core_length(nf);
+  P.m = core_length(n, bc);
   P.logm = ilog2(P.m);
   P.bluestein = P.m != nf;
   // the chirp's period: the DFT length (2 nf for the chirp-z DST-I)
@@ -268,8 +287,10 @@ int PlanCache::get(int n, int bc) {
     }
     for (int k = 0; k < nf; ++k) ctab_.push_back(w[k]);
     std::vector<cl> b(P.m, cl(0, 0));
-    for (int l = 0; l < nf; ++l) b[l] = std::conj(w[l]);
-    for (int l = 1; l < nf; ++l) b[P.m - l] = std::conj(w[l]);
+    // lags k - j in use: see core_length
+    const bool odd = bc == kDirichlet && !P.cz;
+    for (int l = 0; l < (odd ? n : nf); ++l) b[l] = std::conj(w[l]);
+    for (int l = 1; l < (odd ? 2 * n + 1 : nf); ++l) b[P.m - l] = std::conj(w[l]);
     host_fft(b);
     P.off_bhat = (int)ctab_.size();
     for (int k = 0; k < P.m; ++k) ctab_.push_back(b[k] / (long double)P.m);
@@ -404,7 +425,7 @@ int validate3(const double* phi, const double* F, int nx, int ny, int nz, double
   if (v != BHX_OK) return v;
   if (!length_supported(nz, bz, R.precision)) return BHX_ERR_ARG;
   // the three-dimensional column passes (along y and z) have no chirp-z DST-I
-  if (dst_chirp(ny, (bc >> 4) & 15) || dst_chirp(nz, bz)) return BHX_ERR_ARG;
+  if (dst_long(ny, (bc >> 4) & 15) || dst_long(nz, bz)) return BHX_ERR_ARG;
   if ((long long)nx * ny * nz >= (1LL << 31)) return BHX_ERR_ARG;
   return BHX_OK;
 }
@@ -1285,7 +1306,7 @@ int debug_apply(bhx_handle* hd, int op, const double* phi, const double* in, dou
   {
     const AxisPlan PX = hd->plans.plan(hd->plans.get(nx, bcx));
     const AxisPlan PY = hd->plans.plan(hd->plans.get(ny, bcy));
-    make_layout(nx, ny, nz, R.precision, PX.m, PY.m, d3 ? core_length(fft_length(nz, bcz)) : 0,
+    make_layout(nx, ny, nz, R.precision, PX.m, PY.m, d3 ? core_length(nz, bcz) : 0,
                 R.sched.rows_cap, &L, !d3 && use_dense(R, PX, PY));
   }
   const size_t N = (size_t)nx * ny * nz;

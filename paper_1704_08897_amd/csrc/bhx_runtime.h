@@ -83,8 +83,8 @@ inline bool make_layout(int nx, int ny, int prec, int mx, int my, int rows_cap, 
 }
 // Dynamic LDS of the column solve for an axis of n nodes, W columns per item.
 int col_lds(int n, int W, int prec);
-// Core FFT length of a transform of length n (power of two, or Bluestein).
-int core_length(int n);
+// Core FFT length of the transform of an axis (power of two, or Bluestein).
+int core_length(int n, int bc);
 // Spacing of the float64 workspace vectors (elements), 256-byte aligned.
 size_t vec_stride(int nx, int ny);
 // Largest supported transform length for a precision (0 fp64, 1 fp32).
@@ -233,8 +233,9 @@ int prepare_batch(bhx_handle* hd, int n, const InstSpec* specs, const Resolved& 
                   hipStream_t st, Grids* gout);
 int fft_length(int n, int bc);
 // A Dirichlet axis whose DST-I runs as a chirp-z transform of n + 1 points
-// (1024 to 2046 nodes; AxisPlan::cz).
+// (1366 to 2046 nodes; AxisPlan::cz).
 bool dst_chirp(int n, int bc);
+bool dst_long(int n, int bc);
 // Both axes have a dense form (at most kDenseMax nodes).
 bool dense_eligible(const AxisPlan& X, const AxisPlan& Y);
 // Whether an instance with these axes runs the dense-transform passes under
