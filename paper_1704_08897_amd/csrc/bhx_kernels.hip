@@ -725,13 +725,250 @@ __device__ __forceinline__ void fft_fixed(typename V2<R>::T* buf, int rows, int 
   }
 }
 
+// ---------------------------------------------------------------------------
+// Bluestein cores of compile-time length 2^L (kBlueMin <= L <= kBlueMax)
+//
+// The same passes as above with the length, spans, radices and pads as
+// constants.  These kernels issue one vector instruction after the other (FP64
+// ones and address ones at the same rate, two waves per SIMD), so what counts
+// is how many there are: with a constant length every LDS and table address of
+// a thread is one base plus an immediate, and
+//   - the twiddles of span 1 are 1, and no product is made with them;
+//   - where the nf inputs fill no more than half of the core, the odd points of
+//     a span-1 group are zeros, and neither read nor added;
+//   - every transform reads outputs below 2^(L-1) alone, the even points of the
+//     last pass's groups: the odd ones are not made.
+// The sums are not contracted with the products before them, so that the 4-,
+// 8- and 16-point schedules give the same bits.  Whole solves against the
+// run-time-length passes: 1231x877 308 -> 279 ms, 1100x600 145 -> 124 ms, 40
+// mixed instances 92 -> 81 ms, FP32 300x256 130 -> 120 ms.  Cores below 128
+// points stay with those: their axes are short and their rows few.
+// ---------------------------------------------------------------------------
+constexpr int kBlueMin = 7, kBlueMax = 12;
+
+template <typename C> __device__ __forceinline__ C badd(C a, C b) {
+#pragma clang fp contract(off)
+  return mk<C>(a.x + b.x, a.y + b.y);
+}
+template <typename C> __device__ __forceinline__ C bsub(C a, C b) {
+#pragma clang fp contract(off)
+  return mk<C>(a.x - b.x, a.y - b.y);
+}
+__device__ __forceinline__ double bfma(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float bfma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+template <typename C> __device__ __forceinline__ C bmul(C a, C b) {
+#pragma clang fp contract(off)
+  return mk<C>(bfma(a.x, b.x, -(a.y * b.y)), bfma(a.x, b.y, a.y * b.x));
+}
+// dit4 and dif4; ONE: w = 1.
+template <bool ONE, typename C>
+__device__ __forceinline__ void blue_dit4(C& a0, C& a1, C& a2, C& a3, C w2) {
+  const C w1 = ONE ? w2 : bmul(w2, w2);
+  const C u1 = ONE ? a1 : bmul(w1, a1), u3 = ONE ? a3 : bmul(w1, a3);
+  const C t0 = badd(a0, u1), t1 = bsub(a0, u1);
+  const C t2 = badd(a2, u3), t3 = bsub(a2, u3);
+  const C x = ONE ? t2 : bmul(w2, t2), y = cmul_mi(ONE ? t3 : bmul(w2, t3));
+  a0 = badd(t0, x);
+  a2 = bsub(t0, x);
+  a1 = badd(t1, y);
+  a3 = bsub(t1, y);
+}
+template <bool ONE, typename C>
+__device__ __forceinline__ void blue_dif4(C& a0, C& a1, C& a2, C& a3, C tw) {
+  const C w2 = cconj(tw);
+  const C w1 = ONE ? w2 : bmul(w2, w2);
+  const C t0 = badd(a0, a2), d0 = bsub(a0, a2);
+  const C t1 = badd(a1, a3), d1 = bsub(a1, a3);
+  const C x = ONE ? d0 : bmul(d0, w2), y = cmul_pi(ONE ? d1 : bmul(d1, w2));
+  const C e0 = bsub(t0, t1), e1 = bsub(x, y);
+  a0 = badd(t0, t1);
+  a1 = ONE ? e0 : bmul(e0, w1);
+  a2 = badd(x, y);
+  a3 = ONE ? e1 : bmul(e1, w1);
+}
+
+// Pass P of the schedule (W: wide): forward stages (DIT), product with the
+// kernel spectrum (BHAT), inverse stages (DIF).  Pass 0 takes its inputs past nf
+// as zeros on the way in, and leaves the odd points alone on the way out.
+template <typename R, int L, bool W, int P, bool DIT, bool BHAT, bool DIF, bool HALF>
+__device__ __forceinline__ void blue_pass(typename V2<R>::T* buf, int rows,
+                                          BHX_GLOBAL const typename V2<R>::T* twg,
+                                          BHX_GLOBAL const typename V2<R>::T* bhat, int nf) {
+  using C = typename V2<R>::T;
+  constexpr int RAD = fft_pass_rad(L, P, W), LH = fft_pass_lspan(L, P, W);
+  constexpr int LR = RAD == 4 ? 2 : RAD == 8 ? 3 : 4;
+  constexpr int LNB = L - LR, SH = rpos_shift(L);
+  constexpr bool ONE = LH == 0;             // the pass of span 1
+  constexpr int st = rpos_code(1 << L, SH);
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));             // addresses are made per pass, not kept across items
+  for (int u = tid; u < (rows << LNB); u += kThreads) {
+    const int r = u >> LNB, rem = u & ((1 << LNB) - 1);
+    const unsigned k = rem & ((1 << LH) - 1);
+    const unsigned base = ((rem >> LH) << (LR + LH)) + k;
+    // element base + j 2^LH lies a constant past element base: no carry
+    // crosses a pad boundary that j 2^LH alone does not
+    C* a = buf + r * st + rpos_code((int)base, SH);
+    // twiddles of the spans 2^LH and 2^(LH+2), W_4h^k and W_16h^(k + q h)
+    auto wa = [&]() -> C {
+      if constexpr (ONE || RAD == 8) return mk<C>(1, 0);
+      else return twg[k << (L - 2 - LH)];
+    };
+    auto wb = [&](int q) -> C {
+      if constexpr (ONE)                    // W_16^q
+        return q == 1   ? mk<C>((R)0.92387953251128675612818318939678829L,
+                                (R)-0.38268343236508977172845998403039887L)
+               : q == 2 ? mk<C>((R)0.70710678118654752440084436210484904L,
+                                (R)-0.70710678118654752440084436210484904L)
+                        : mk<C>((R)0.38268343236508977172845998403039887L,
+                                (R)-0.92387953251128675612818318939678829L);
+      else
+        return (twg + (q << (L - 4)))[k << (L >= 4 + LH ? L - 4 - LH : 0)];
+    };
+    const C w8 = mk<C>((R)0.70710678118654752440084436210484904L,
+                       (R)-0.70710678118654752440084436210484904L);
+    constexpr bool ZIN = DIT && P == 0;     // inputs past nf are zeros
+    constexpr bool EVEN = DIF && P == 0;    // even outputs alone
+    C v[RAD];
+#pragma unroll
+    for (int j = 0; j < RAD; ++j) {
+      if (ZIN && HALF && (j & 1)) continue;
+      v[j] = a[rpos_code(j << LH, SH)];
+    }
+    if constexpr (ZIN) {
+      const int rb = bitrev((int)base, L);  // base is a multiple of RAD here
+#pragma unroll
+      for (int j = 0; j < RAD; ++j) {
+        if (HALF && (j & 1)) continue;
+        const int q = rb + (bitrev(j, LR) << (L - LR));
+        v[j] = q < nf ? v[j] : mk<C>(0, 0);
+      }
+    }
+    if constexpr (DIT) {
+      if constexpr (RAD == 8) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          if (ZIN && HALF) {
+            v[2 * q + 1] = v[2 * q];
+          } else {
+            const C x = v[2 * q], y = v[2 * q + 1];
+            v[2 * q] = badd(x, y);
+            v[2 * q + 1] = bsub(x, y);
+          }
+        }
+        blue_dit4<true>(v[0], v[2], v[4], v[6], w8);
+        blue_dit4<false>(v[1], v[3], v[5], v[7], w8);
+      } else {
+        const C w = wa();
+#pragma unroll
+        for (int q = 0; q < RAD / 4; ++q) {
+          if (ZIN && HALF) {
+            const C x = v[4 * q], y = v[4 * q + 2], z = cmul_mi(y);
+            v[4 * q] = badd(x, y);
+            v[4 * q + 2] = bsub(x, y);
+            v[4 * q + 1] = badd(x, z);
+            v[4 * q + 3] = bsub(x, z);
+          } else {
+            blue_dit4<ONE>(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3], w);
+          }
+        }
+        if constexpr (RAD == 16) {
+          blue_dit4<ONE>(v[0], v[4], v[8], v[12], ONE ? w : wb(0));
+#pragma unroll
+          for (int q = 1; q < 4; ++q)
+            blue_dit4<false>(v[q], v[q + 4], v[q + 8], v[q + 12], wb(q));
+        }
+      }
+    }
+    if constexpr (BHAT) {
+#pragma unroll
+      for (int j = 0; j < RAD; ++j) v[j] = bmul(v[j], (bhat + (j << LH))[base]);
+    }
+    if constexpr (DIF) {
+      if constexpr (RAD == 8) {
+        blue_dif4<true>(v[0], v[2], v[4], v[6], w8);
+        blue_dif4<false>(v[1], v[3], v[5], v[7], w8);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const C x = v[2 * q], y = v[2 * q + 1];
+          v[2 * q] = badd(x, y);
+          if (!EVEN) v[2 * q + 1] = bsub(x, y);
+        }
+      } else {
+        if constexpr (RAD == 16) {
+          blue_dif4<ONE>(v[0], v[4], v[8], v[12], ONE ? mk<C>(1, 0) : wb(0));
+#pragma unroll
+          for (int q = 1; q < 4; ++q)
+            blue_dif4<false>(v[q], v[q + 4], v[q + 8], v[q + 12], wb(q));
+        }
+        const C w = wa();
+#pragma unroll
+        for (int q = 0; q < RAD / 4; ++q)
+          blue_dif4<ONE>(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3], w);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < RAD; ++j) {
+      if (EVEN && (j & 1)) continue;
+      a[rpos_code(j << LH, SH)] = v[j];
+    }
+  }
+  __syncthreads();
+}
+
+// Passes P.. forward, the joint last one, and back.
+template <typename R, int L, bool W, int P>
+__device__ __forceinline__ void blue_passes(typename V2<R>::T* buf, int rows,
+                                            BHX_GLOBAL const typename V2<R>::T* twg,
+                                            BHX_GLOBAL const typename V2<R>::T* bhat, int nf) {
+  constexpr bool last = P == fft_npass(L, W) - 1;
+  if constexpr (P == 0) {
+    if (nf <= 1 << (L - 1))
+      blue_pass<R, L, W, 0, true, false, false, true>(buf, rows, twg, bhat, nf);
+    else
+      blue_pass<R, L, W, 0, true, false, false, false>(buf, rows, twg, bhat, nf);
+  } else {
+    blue_pass<R, L, W, P, true, last, last, false>(buf, rows, twg, bhat, nf);
+  }
+  if constexpr (!last) {
+    blue_passes<R, L, W, P + 1>(buf, rows, twg, bhat, nf);
+    blue_pass<R, L, W, P, false, false, true, false>(buf, rows, twg, bhat, nf);
+  }
+}
+
+// Runs rows of core length 2^L here if that length is compiled (returns true).
+template <typename R, bool W, int L = kBlueMax>
+__device__ __forceinline__ bool blue_core(typename V2<R>::T* buf, int rows, int logm,
+                                          BHX_GLOBAL const typename V2<R>::T* twg,
+                                          BHX_GLOBAL const typename V2<R>::T* bhat, int nf) {
+  if constexpr (L >= kBlueMin) {
+    if (logm == L) {
+      // 2^L >= kFftWideMin rows take the wide schedule in the wide families;
+      // the narrow family has launches of less than kFftWideLaunch points
+      if constexpr (W) {
+        if ((rows << L) >= kFftWideMin)
+          blue_passes<R, L, true, 0>(buf, rows, twg, bhat, nf);
+        else if constexpr ((1 << L) < kFftWideMin)
+          blue_passes<R, L, false, 0>(buf, rows, twg, bhat, nf);
+      } else {
+        if constexpr ((1 << L) < kFftWideLaunch)
+          blue_passes<R, L, false, 0>(buf, rows, twg, bhat, nf);
+      }
+      return true;
+    }
+    return blue_core<R, W, L - 1>(buf, rows, logm, twg, bhat, nf);
+  } else {
+    return false;
+  }
+}
+
 // After inputs are placed at pos(k) (k < nf): the forward DFT of length nf of
 // every row.  Power-of-two nf: the FFT passes, natural-order output.
 // Otherwise Bluestein: chirp (applied already if CHIRPED; zero past nf), FFT,
 // product with the kernel spectrum, inverse FFT (bit-reversed output; out()
 // applies the final chirp).
 template <bool W, bool CHIRPED, typename R, int SP>
-__device__ void dft_core(const XPlan<R, SP>& X, typename V2<R>::T* buf, int rows) {
+__device__ __forceinline__ void dft_core(const XPlan<R, SP>& X, typename V2<R>::T* buf, int rows) {
   if constexpr (SP != 0) {
     constexpr int L = (SP >> 2) & 63;
     // rows is a constant of the instance here
@@ -747,6 +984,9 @@ __device__ void dft_core(const XPlan<R, SP>& X, typename V2<R>::T* buf, int rows
     const bool wide = W && (rows << logm) >= kFftWideMin;
     const int np = fft_npass(logm, wide);
     const bool blue = X.blue;
+    if constexpr (CHIRPED) {
+      if (blue && blue_core<R, W>(buf, rows, logm, X.twg, X.bhat, X.nf)) return;
+    }
     // steps 0..np-1: forward passes; then (Bluestein) passes np-2..0 inverse
     const int nstep = blue ? 2 * np - 1 : np;
 #pragma unroll 1
@@ -1331,7 +1571,7 @@ __global__ void __launch_bounds__(kThreads) k_resid(const Batch* __restrict__ Bp
 // p[lpar ^ 1], current r.z partials rz(lpar).  SP: compile-time shape of the
 // x axis and row group (see XPlan), 0 for any shape.
 template <typename R, int SP, int FAM = 0>
-__global__ void __launch_bounds__(kThreads) k_rowfwd(const Batch* __restrict__ Bp, int update,
+__global__ void __launch_bounds__(kThreads, FAM == kFamCz ? 2 : 1) k_rowfwd(const Batch* __restrict__ Bp, int update,
                                                      int twoff, int lpar) {
   using C = typename V2<R>::T;
   constexpr bool CZ = FAM == kFamCz;

@@ -70,3 +70,37 @@ def test_sine_core_lengths(handle, n, prec):
 def test_sine_core_lengths_3d(handle, n):
     """Along y of three dimensions, both sides of an edge."""
     check(handle, (5, n, 9), (0, 2, 1), 0)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("n", [33, 63, 65, 100, 127, 129, 255, 257, 300, 511, 513, 1000, 1023,
+                               1025, 1231, 2047])
+def test_core_lengths(handle, n, prec):
+    """Both ends of every core length, Neumann and periodic rows; few and many
+    lines (short and long work items)."""
+    for ny, rules in ((5, (0, 1)), (40, (1, 0)), (130, (0, 0))):
+        check(handle, (ny, n), rules, prec)
+
+
+@pytest.mark.parametrize("rules", [(0, 0), (1, 1), (2, 2)])
+def test_batch_gives_the_single_solves_bits(handle, rules):
+    """Schedules of 4, 8 and 16 points: an instance alone and beside a longer
+    one, which takes the launch to another kernel family."""
+    sizes = [(75, 70), (150, 90), (300, 180), (700, 100)]
+    ins = []
+    for nx, ny in sizes:
+        y, x = np.meshgrid(np.linspace(-1, 1, ny), np.linspace(-1, 1, nx), indexing="ij")
+        ins.append((dev(np.hypot(x, y) - 0.5), dev(np.cos(2 * x) + np.sin(y))))
+    alone = []
+    for phi, F in ins:
+        G = F.clone()
+        s, _ = bhx.extend_ex(handle, phi, G, h=0.01, bc=bhx.BC(*rules), tol=1e-10)
+        assert s == bhx.OK
+        alone.append(G)
+    outs = [F.clone() for _, F in ins]
+    k = len(ins)
+    s, _ = bhx.extend_batched(handle, [p for p, _ in ins], outs, [0.01] * k,
+                              [bhx.BC(*rules)] * k, [1e-10] * k)
+    assert s == bhx.OK
+    for a, b in zip(alone, outs):
+        assert torch.equal(a, b)
