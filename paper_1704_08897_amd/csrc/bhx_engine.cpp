@@ -213,7 +213,6 @@ Grids engine_grids(bhx_engine* E, const std::vector<Req*>& reqs) {
   Grids g{};
   const int cu = E->hd->num_cu;
   g.s = cu * 8;
-  g.r = cu * 2;
   g.c = cu * 2;
   const int csize = E->R.precision == 0 ? 16 : 8;
   int buf_r = 0, lds_c = 0;
@@ -238,6 +237,7 @@ Grids engine_grids(bhx_engine* E, const std::vector<Req*>& reqs) {
   auto up = [](int b) { return (b + 4095) / 4096 * 4096; };
   g.tw_r = buf_r;
   g.lds_r = std::min(kLdsDynMax, up(buf_r * csize));
+  g.r = cu * row_occupancy(g.shape_r, g.lds_r);
   g.tw_c = 0;
   g.lds_c = std::min(kLdsDynMax, up(lds_c));
   // the FFT family launches every iteration (with no request on it it

@@ -31,6 +31,7 @@ constexpr int kTileY3 = 8;
 constexpr int kTileZ3 = 4;
 constexpr int kLdsBytes = 80 * 1024;   // LDS for the packed rows of one transform item
 constexpr int kLdsMax = 160 * 1024;    // LDS of a CU (gfx950)
+constexpr int kLdsCu = 160 * 1024;     // LDS of a CU
 constexpr int kLdsDynMax = 152 * 1024; // dynamic LDS cap of a transform launch
 constexpr int kMaxPairs = 8;           // (k, n-k) pairs held in registers per thread
 constexpr int kMaxGc = 16;             // y pencils per item (three dimensions)
@@ -317,6 +318,10 @@ constexpr int kShapeCzKey = 1;
 constexpr int kShapeWideKey = 2;
 enum PlanFamily { kFamNarrow = 0, kFamWide = 1, kFamCz = 2 };
 constexpr int kFftWideLaunch = 4096;
+// Blocks per CU that the registers of a row kernel leave room for.
+__host__ __device__ constexpr int row_blocks(int shape, int fam) {
+  return shape != 0 ? 1 : fam == kFamNarrow ? 4 : 2;
+}
 // Plan-table families take the shape values below 2^8; compile-time shapes
 // have G >= 2 in bits 8 and up.
 inline bool plan_table_shape(int shape) { return shape < 256; }

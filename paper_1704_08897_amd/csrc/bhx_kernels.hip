@@ -1571,8 +1571,8 @@ __global__ void __launch_bounds__(kThreads) k_resid(const Batch* __restrict__ Bp
 // p[lpar ^ 1], current r.z partials rz(lpar).  SP: compile-time shape of the
 // x axis and row group (see XPlan), 0 for any shape.
 template <typename R, int SP, int FAM = 0>
-__global__ void __launch_bounds__(kThreads, FAM == kFamCz ? 2 : 1) k_rowfwd(const Batch* __restrict__ Bp, int update,
-                                                     int twoff, int lpar) {
+__global__ void __launch_bounds__(kThreads, row_blocks(SP, FAM))
+    k_rowfwd(const Batch* __restrict__ Bp, int update, int twoff, int lpar) {
   using C = typename V2<R>::T;
   constexpr bool CZ = FAM == kFamCz;
   constexpr bool kWide = FAM != kFamNarrow;
@@ -1616,7 +1616,7 @@ __global__ void __launch_bounds__(kThreads, FAM == kFamCz ? 2 : 1) k_rowfwd(cons
     Partials<2> PS;
     sums_issue<2>(arrs, lens, PS);             // unconditional: no branch before the loads
     const double rsc[2] = {ctl->red_rz[lpar], ctl->red_pq};
-    constexpr int kPair = kPre / 2;
+    constexpr int kPair = SP == 0 && FAM == kFamNarrow ? 3 : kPre / 2;
     const int S = rows * nx;                   // samples
     int o0[kPair], ma0[kPair], mb0[kPair];
 #pragma unroll
@@ -2524,7 +2524,7 @@ __global__ void __launch_bounds__(kThreads) k_ypass(const Batch* __restrict__ Bp
 // the next iteration's current ones, rz(lpar ^ 1) (and rzo(lpar ^ 1)).  SP as
 // in k_rowfwd.
 template <typename R, int SP, int FAM = 0>
-__global__ void __launch_bounds__(kThreads, FAM == kFamCz ? 1 : 2)
+__global__ void __launch_bounds__(kThreads, row_blocks(SP, FAM))
     k_rowinv(const Batch* __restrict__ Bp, int twoff, int lpar) {
   using C = typename V2<R>::T;
   constexpr bool CZ = FAM == kFamCz;

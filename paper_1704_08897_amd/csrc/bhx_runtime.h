@@ -91,10 +91,10 @@ size_t vec_stride(int nx, int ny);
 bool length_supported(int n, int prec);
 
 // Launch schedule: packed rows per transform item (0 = policy), persistent
-// blocks per CU of the stencil / row / column passes.
+// blocks per CU of the stencil / row / column passes (occ_r = 0: row_occupancy).
 struct Schedule {
   int rows_cap = 0;
-  int occ_s = 8, occ_r = 2, occ_c = 2;
+  int occ_s = 8, occ_r = 0, occ_c = 2;
   int chunk = 0;             // 0 = option's chunk
   int transform = -1;        // -1: the option's; else 0 policy, 1 FFT, 2 dense where possible
   int occ_d = 2;             // persistent blocks per CU of the dense-transform passes
@@ -248,6 +248,9 @@ void dense_grids(int prec, int nx_max, int ny_max, int n_rd, int n_cd, int num_c
 // Plan indices and layouts of a batch (host only).
 int plan_layouts(PlanCache& plans, int n, const InstSpec* specs, const Resolved& R,
                  BatchDesc* D);
+// Persistent blocks per CU of the row passes for kernels of shape key `shape`
+// with `lds` bytes of dynamic LDS.
+int row_occupancy(int shape, int lds);
 // Bytes of the control-block region at the start of a batch workspace.
 size_t ctl_region_bytes(int n);
 // Descriptors, work lists and control blocks of a batch whose workspace
