@@ -24,14 +24,19 @@
 namespace bhx {
 
 constexpr int kThreads = 256;          // threads per workgroup, every kernel
-constexpr int kTileX = 64;             // stencil tile (nodes), two dimensions
-constexpr int kTileY = 32;
+// Stencil tile (nodes), two dimensions.  A pass over a tile is one chain of
+// waits (control block, halo, partial sums, two stages through LDS), so what
+// helps is tiles in flight: 16 rows give twice the blocks of 32, with four
+// instead of three on a CU.  Stencil pass with 32 -> 16 rows: 64x64 7.5 -> 6.4
+// us, 450x450 9.4 -> 7.7, 1231x877 18.4 -> 16.0, eight served requests 35.8 ->
+// 23.4; 1024x1024 of which one tile in eight has unknown nodes 9.5 -> 10.7.
+constexpr int kTileX = 64;
+constexpr int kTileY = 16;
 constexpr int kTileX3 = 16;            // stencil tile (nodes), three dimensions
 constexpr int kTileY3 = 8;
 constexpr int kTileZ3 = 4;
 constexpr int kLdsBytes = 80 * 1024;   // LDS for the packed rows of one transform item
 constexpr int kLdsMax = 160 * 1024;    // LDS of a CU (gfx950)
-constexpr int kLdsCu = 160 * 1024;     // LDS of a CU
 constexpr int kLdsDynMax = 152 * 1024; // dynamic LDS cap of a transform launch
 constexpr int kMaxPairs = 8;           // (k, n-k) pairs held in registers per thread
 constexpr int kMaxGc = 16;             // y pencils per item (three dimensions)
@@ -39,6 +44,9 @@ constexpr int kColThreads = 512;       // threads of the column solve
 constexpr int kColWaves = kColThreads / 64;
 constexpr int kColWide = 4 * kColWaves;   // columns of its wide items (16 lanes a column),
                                        // else kColWaves (64 lanes)
+// Wide items need an axis whose 32 columns fit LDS in FP64 beside a second block,
+// and enough columns to give every CU a block; in two dimensions one instance
+// has fewer (128 items of 32 columns leave half the CUs idle).
 constexpr int kColWideMax = 512;       // longest axis of wide items
 constexpr int kColWideMin = 4096;      // columns one instance needs for wide items
 constexpr int kTargetItems = 512;      // row/column items one instance should supply

@@ -232,6 +232,7 @@ __device__ __forceinline__ void sums_finish(BHX_GLOBAL const double* const (&a)[
     s[k] = 0.0;
 #pragma unroll
     for (int u = 0; u < 4; ++u) s[k] += (u * kThreads + (int)threadIdx.x < n[k]) ? P.v[k][u] : 0.0;
+#pragma unroll 4
     for (int i = 4 * kThreads + threadIdx.x; i < n[k]; i += kThreads) s[k] += a[k][i];
   }
   const int w = threadIdx.x >> 6;
@@ -359,12 +360,9 @@ struct XPlan {
   BHX_GLOBAL const C* chirp;
   BHX_GLOBAL const C* bhat;
   BHX_GLOBAL const C* post;
-  BHX_GLOBAL const R* lam;
   const C* postl;             // post-twiddles of the pairs' first members, in LDS
-  const R* laml;              // eigenvalues of the pairs' first members, in LDS
-  // Copy the plan's twiddles, the DCT post-twiddles and (with `with_lam`,
-  // for passes that scale) the eigenvalues of the pairs' first members into
-  // LDS at `lds` (table_slots(n, m, bc, with_lam) complex slots) unless plan
+  // Copy the plan's twiddles and the DCT post-twiddles of the pairs' first
+  // members into LDS at `lds` (table_slots(n, m, bc, false) complex slots) unless plan
   // `idx` is staged there already; every thread of the block must call this
   // at the same point.  The twiddles are laid out per radix-4 stage of span
   // h: W_4h^k for k < h (stage_twiddles), so each stage reads them at unit
@@ -372,7 +370,7 @@ struct XPlan {
   // flat index space in rounds of kStageRound entries per thread, all loads of
   // a round issued before its LDS writes: one or two memory round trips per
   // launch instead of one per table.
-  __device__ void stage(C* lds, int idx, int& staged, bool with_lam) {
+  __device__ void stage(C* lds, int idx, int& staged) {
     if constexpr (SP == 0) {
       // plan-table instances read every table from global memory (L2): the
       // LDS holds the packed rows alone, so two work items fit on a CU even
@@ -383,13 +381,11 @@ struct XPlan {
     const int ntw = stage_twiddles(logm);
     C* tw_l = lds;
     C* post_l = lds + ntw;
-    R* lam_l = (R*)(post_l + (bc == kNeumann ? np : 0));
     if (idx != staged) {
       const int nc = ntw + (bc == kNeumann ? np : 0);   // complex entries
-      const int nl = with_lam ? np : 0;                  // real entries
       const int h0 = (logm & 1) ? 2 : 1;
-      for (int base = 0; base < max(nc, nl); base += kStageRound * kThreads) {
-        R vr[kStageRound], vi[kStageRound], vl[kStageRound];   // real arrays stay in VGPRs
+      for (int base = 0; base < nc; base += kStageRound * kThreads) {
+        R vr[kStageRound], vi[kStageRound];   // real arrays stay in VGPRs
 #pragma unroll
         for (int u = 0; u < kStageRound; ++u) {
           const int e = base + (int)threadIdx.x + u * kThreads;
@@ -406,13 +402,11 @@ struct XPlan {
           }
           vr[u] = v.x;
           vi[u] = v.y;
-          vl[u] = e < nl ? lam[e] : (R)0;
         }
 #pragma unroll
         for (int u = 0; u < kStageRound; ++u) {
           const int e = base + (int)threadIdx.x + u * kThreads;
           if (e < nc) tw_l[e] = mk<C>(vr[u], vi[u]);
-          if (e < nl) lam_l[e] = vl[u];
         }
       }
       __syncthreads();
@@ -420,7 +414,6 @@ struct XPlan {
     }
     tw = tw_l;
     postl = post_l;
-    laml = lam_l;
   }
   __device__ XPlan(const Batch& B, int idx) {
     const AxisPlan P = B.plans[idx];
@@ -442,11 +435,9 @@ struct XPlan {
     twg = ct + P.off_tw;
     tw = nullptr;
     postl = nullptr;
-    laml = nullptr;
     chirp = ct + P.off_chirp;
     bhat = ct + P.off_bhat;
     post = ct + P.off_post;
-    lam = (BHX_GLOBAL const R*)B.rtab[pi] + P.off_lam;
   }
   // LDS position of logical FFT input k (bit-reversed)
   __device__ __forceinline__ int pos(int k) const { return rpos(bitrev(k, logm), sh); }
@@ -468,15 +459,6 @@ struct XPlan {
     else
       tk = postl[k];
     tkk = kk == k ? tk : mk<C>(-tk.y, -tk.x);
-  }
-  // eigenvalues of the pair: lambda[partner] = lambda[k] for the periodic
-  // axis, 4 - lambda[k] for the DCT and DST-I ones (4 sin^2 -> 4 cos^2)
-  __device__ __forceinline__ void lam_pair(int k, int kk, R& lk, R& lkk) const {
-    if constexpr (SP == 0)
-      lk = lam[k];
-    else
-      lk = laml[k];
-    lkk = kk == k ? lk : (bc == kPeriodic ? lk : (R)4 - lk);
   }
   __device__ __forceinline__ int partner(int k) const {
     return bc == kDirichlet ? n - 1 - k : (k == 0 ? 0 : n - k);
@@ -1221,7 +1203,7 @@ constexpr int kPre = 8;                             // elements per thread loade
 // Three dimensions: at most 168 VGPRs, three waves per SIMD (more tiles in
 // flight per CU; measured faster than two with more registers).
 template <int MODE, int DIM>
-__global__ void __launch_bounds__(kThreads, DIM == 3 ? 3 : 2)
+__global__ void __launch_bounds__(kThreads, DIM == 3 ? 3 : 4)
     k_stencil(const Batch* __restrict__ Bp, int lpar) {
   using G = Geo<DIM>;
   constexpr int kPN = G::PX * G::PY * G::PZ;               // halo tile nodes
@@ -1244,6 +1226,10 @@ __global__ void __launch_bounds__(kThreads, DIM == 3 ? 3 : 2)
     const int code = item_code(B, kPassS, it);
     const Inst I = B.inst[code >> kItemShift];
     const int tile = code & kItemMask;
+    // node coordinates are made per item in two dimensions: kept across the
+    // item loop they would cost a block its registers
+    int tid = threadIdx.x;
+    if constexpr (DIM == 2) asm volatile("" : "+v"(tid));
     BHX_GLOBAL Ctl* ctl = I.ctl;
     const PartLayout PL(I.n_items[kPassS], I.n_items[kPassR]);
     // 1. loads that need nothing from the control block go out with it: the
@@ -1258,6 +1244,11 @@ __global__ void __launch_bounds__(kThreads, DIM == 3 ? 3 : 2)
     // its partial loads shrink to one element (no branch before the loads)
     const int nRs = I.reduce ? 1 : PL.nR;
     const int lens[4] = {nRs, nRs, nRs, nRs};
+    // `done` and the tile's unknown nodes first: loads return in order, so a
+    // tile without any leaves without waiting for the partial sums
+    const int ld_done = ctl->done;
+    const bool has_u = I.part[PL.aux2() + tile] != 0.0;
+    __builtin_amdgcn_sched_barrier(0);
     Partials<4> PS;
     if (MODE == kModeIter) sums_issue<4>(arrs, lens, PS);
     double rsc[4] = {0.0, 0.0, 0.0, 0.0};
@@ -1267,11 +1258,9 @@ __global__ void __launch_bounds__(kThreads, DIM == 3 ? 3 : 2)
       rsc[2] = ctl->red_rz[par ^ 1];
       rsc[3] = ctl->red_rzo[par];
     }
-    const int ld_done = ctl->done;
     const int c_iter = ctl->iter, c_rit = ctl->restart_iter;
     const double c_thresh = ctl->thresh;
-    const bool has_u = I.part[PL.aux2() + tile] != 0.0;     // unknown nodes in this tile
-    if (threadIdx.x == 0) s_done[slot] = ld_done;
+    if (tid == 0) s_done[slot] = ld_done;
     __syncthreads();
     const int c_done = s_done[slot];
     slot ^= 1;
@@ -1279,7 +1268,7 @@ __global__ void __launch_bounds__(kThreads, DIM == 3 ? 3 : 2)
     const int nx = I.nx, ny = I.ny, nz = I.nz;
     const int out_slot = (MODE == kModeIter ? PL.pq() : PL.aux()) + tile;
     if (!has_u && tile != 0) {             // nothing to compute or store here
-      if (threadIdx.x == 0) I.part[out_slot] = 0.0;
+      if (tid == 0) I.part[out_slot] = 0.0;
       continue;
     }
     // 2. the halo tile (z and p_old, or F, and the mask) and the output masks
@@ -1303,7 +1292,7 @@ __global__ void __launch_bounds__(kThreads, DIM == 3 ? 3 : 2)
                               : ((k0 - 2) * ny + (j0 - 2)) * nx + (i0 - 2);
 #pragma unroll
     for (int s = 0; s < kPL; ++s) {
-      const int e = min((int)threadIdx.x + s * kThreads, kPN - 1);
+      const int e = min(tid + s * kThreads, kPN - 1);
       int ii, jj, kk;
       G::template coords<G::PX, G::PY>(e, ii, jj, kk);
       if (interior) {
@@ -1340,7 +1329,7 @@ __global__ void __launch_bounds__(kThreads, DIM == 3 ? 3 : 2)
     }
 #pragma unroll
     for (int s = 0; s < kOut; ++s) {
-      const int e = threadIdx.x + s * kThreads;
+      const int e = tid + s * kThreads;
       int ii, jj, kk;
       G::template coords<G::TX, G::TY>(e, ii, jj, kk);
       const int gi = min(i0 + ii, nx - 1), gj = min(j0 + jj, ny - 1);
@@ -1370,7 +1359,7 @@ __global__ void __launch_bounds__(kThreads, DIM == 3 ? 3 : 2)
           d = kConverged;
         }
         if (d != kRunning) {
-          if (tile == 0 && threadIdx.x == 0) {
+          if (tile == 0 && tid == 0) {
             ctl->rr = rr;
             ctl->done = d;
           }
@@ -1379,18 +1368,18 @@ __global__ void __launch_bounds__(kThreads, DIM == 3 ? 3 : 2)
         beta = I.flexible ? (rz - sums[3]) / sums[2] : rz / sums[2];
       }
       if (!(rz > 0.0) || !(beta == beta)) {
-        if (tile == 0 && threadIdx.x == 0) ctl->done = kBreakdown;
+        if (tile == 0 && tid == 0) ctl->done = kBreakdown;
         continue;
       }
     }
     if (!has_u) {
-      if (threadIdx.x == 0) I.part[out_slot] = 0.0;
+      if (tid == 0) I.part[out_slot] = 0.0;
       continue;
     }
     // 4. tile of the operand in LDS, L f on the one-node ring, then L L f
 #pragma unroll
     for (int s = 0; s < kPL; ++s) {
-      const int e = threadIdx.x + s * kThreads;
+      const int e = tid + s * kThreads;
       double v;
       if (MODE == kModeIter) v = first ? va[s] : va[s] + beta * vb[s];
       else if (MODE == kModeRhs) v = vm[s] ? 0.0 : va[s];
@@ -1403,7 +1392,7 @@ __global__ void __launch_bounds__(kThreads, DIM == 3 ? 3 : 2)
       }
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < G::LX * G::LY * G::LZ; e += kThreads) {
+    for (int e = tid; e < G::LX * G::LY * G::LZ; e += kThreads) {
       int ii, jj, kk;
       G::template coords<G::LX, G::LY>(e, ii, jj, kk);
       L[kk][jj][ii] = G::lap(P, kk + G::HZ, jj + 1, ii + 1);
@@ -1412,7 +1401,7 @@ __global__ void __launch_bounds__(kThreads, DIM == 3 ? 3 : 2)
     double acc = 0.0;
 #pragma unroll
     for (int s = 0; s < kOut; ++s) {
-      const int e = threadIdx.x + s * kThreads;
+      const int e = tid + s * kThreads;
       int ii, jj, kk;
       G::template coords<G::TX, G::TY>(e, ii, jj, kk);
       const int gi = i0 + ii, gj = j0 + jj, gk = k0 + kk;
@@ -1434,7 +1423,7 @@ __global__ void __launch_bounds__(kThreads, DIM == 3 ? 3 : 2)
       }
     }
     acc = block_sum(acc, red);
-    if (threadIdx.x == 0) I.part[out_slot] = acc;
+    if (tid == 0) I.part[out_slot] = acc;
   }
 }
 
@@ -1655,7 +1644,7 @@ __global__ void __launch_bounds__(kThreads, row_blocks(SP, FAM))
     }
     XPlan<R, SP> X(B, I.planx);
     if constexpr (!CZ) X.cz = 0;   // chirp-z axes run on the CZ instances only
-    if (update != 2) X.stage(twl, I.planx, staged, false);
+    if (update != 2) X.stage(twl, I.planx, staged);
     double alpha = 0.0;
     if (update) {
       double sums[2];
@@ -1798,7 +1787,10 @@ __global__ void __launch_bounds__(kThreads, row_blocks(SP, FAM))
 //
 // Bound: memory and launch latency up to about 1024^2 nodes, HBM beyond (16
 // bytes and about 20 operations per node in FP64).  The transforms it replaces
-// cost two FFTs per column, four of twice the length where Bluestein runs.
+// cost two FFTs per column, four of twice the length where Bluestein runs.  Per
+// launch, transforms -> recursions: 1024^2 12.1 -> 10.7 us, 2048^2 32.2 -> 17.9
+// (64 MB, 3.7 TB/s), 450^2 19.5 -> 7.3, 1231x877 69.2 -> 12.6 (17 MB, 1.4 TB/s),
+// 40 mixed instances 82.4 -> 13.2, 128^3 along z 21.0 -> 12.9.
 // Relative to the spectral form its rounding is smaller in the energy norm
 // that conjugate gradients work in (about 1e-11 against 1e-10 at 2048 nodes
 // and the smallest lambda).
@@ -2389,7 +2381,7 @@ __global__ void __launch_bounds__(kThreads) k_ypass(const Batch* __restrict__ Bp
     if (ctl->done) continue;
     XPlan<R, SP> X(B, I.plany);
     X.cz = 0;                        // no chirp-z axis in three dimensions
-    X.stage(twl, I.plany, staged, false);
+    X.stage(twl, I.plany, staged);
     const int rows = Gp >> 1;
     const int st = X.stride();
     const int np = X.pairs();
@@ -2606,7 +2598,7 @@ __global__ void __launch_bounds__(kThreads, row_blocks(SP, FAM))
     }
     XPlan<R, SP> X(B, I.planx);
     if constexpr (!CZ) X.cz = 0;   // chirp-z axes run on the CZ instances only
-    X.stage(twl, I.planx, staged, false);
+    X.stage(twl, I.planx, staged);
     const int st = X.stride();
     double acc = 0.0, acco = 0.0;
     if (X.cz) {

@@ -5,6 +5,7 @@
 // itself allocates no device or pinned memory.  The kernels are the ones of
 // the handle path; only where their buffers live differs, and the iteration
 // chunks are launched directly instead of from captured graphs.
+#include <algorithm>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -16,10 +17,14 @@ namespace bhx {
 namespace {
 
 constexpr size_t kScratchBytes = (size_t)BHX_NOALLOC_SCRATCH_BYTES;
+// The limit counts tiles of 32 rows.  The halves of a tile (kTileY rows) keep
+// their partial sums and list entries past it: 28 bytes a tile, fewer than 2600
+// tiles for what fits.
+constexpr size_t kScratchSlack = 128 << 10;
 constexpr int kMaxDevices = 64;
 
 // One copy per device; its device address is looked up once per device.
-__device__ __align__(256) unsigned char scratch[kScratchBytes];
+__device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchSlack];
 
 std::mutex g_lookup_mu;
 void* g_scratch_ptr[kMaxDevices] = {};
@@ -111,7 +116,10 @@ int solve_noalloc(bhx_handle* hd, const InstSpec& spec, const Resolved& R, hipSt
   const size_t o_rf = o;    o = up256(o + rf.size() * sizeof(float));
   const size_t o_flag = o;  o = up256(o + sizeof(int));
   const size_t o_ws = o;    o = up256(o + D.ws_bytes);
-  if (o > cap) {
+  const size_t halves = (size_t)D.inst[0].tiles_x *
+                        (D.inst[0].tiles_y - (spec.ny + 2 * kTileY - 1) / (2 * kTileY));
+  const size_t past = halves * (3 * sizeof(double) + sizeof(int));
+  if (o > cap + std::min(past, kScratchSlack)) {
     char msg[200];
     snprintf(msg, sizeof(msg),
              "bhx_extend_noalloc: %dx%d needs %zu bytes of scratch, the limit is %zu", spec.nx,

@@ -889,7 +889,7 @@ void dense_grids(int prec, int nx_max, int ny_max, int n_rd, int n_cd, int num_c
 // other kernels hold two blocks' worth of registers.
 int row_occupancy(int shape, int lds) {
   if (shape != kShapeNarrowKey) return 2;
-  return std::max(2, std::min(row_blocks(0, kFamNarrow), kLdsCu / std::max(1, lds + 256)));
+  return std::max(2, std::min(row_blocks(0, kFamNarrow), kLdsMax / std::max(1, lds + 256)));
 }
 
 int batch_grids(const PlanCache& plans, const BatchDesc& D, const Resolved& R, int num_cu,
