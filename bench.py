@@ -26,10 +26,7 @@ periodic_circles_2048(_fp64), batch256, example2_256, example4_channel.
 
 Prints ONE JSON line (last line of stdout).  Progress goes to stderr.  Its
 `roofline` is the HBM view of the dominant pass (algorithmic bytes per launch
-over the launch's time); for the serving stream,
-`roofline.column_pass_compute_view` gives the same launches' FP64 flop rate
-against the vector peak, since chirp-z cores put the column pass above the
-FP64 ridge.
+over the launch's time).
 """
 import argparse
 import hashlib
@@ -45,9 +42,8 @@ sys.path.insert(0, ROOT)
 
 METRIC = "extension solves/sec + p50/p99 latency at 1e-8 rel. residual; HBM GB/s"
 HBM_PEAK_GBS = 8000.0
-FP64_VECTOR_PEAK_TFLOPS = 78.6
 PASS_NAMES = ["stencil", "row_forward", "column", "row_inverse"]
-PASS_KERNELS = ["k_stencil", "k_rowfwd", "k_col", "k_rowinv"]
+PASS_KERNELS = ["k_stencil", "k_rowfwd", "k_colsolve", "k_rowinv"]
 
 
 def log(*a):
@@ -86,8 +82,9 @@ def pass_coeffs(p, prec):
 
 
 def column_pass_flops(n):
-    """Algorithmic FP64 flops of one 2-D column-pass launch over an n x n grid
-    with a Neumann or periodic y axis, by the usual count of 5 m log2(m) per
+    """FP64 flops that a spectral column pass over an n x n grid with a Neumann
+    or periodic y axis takes (the column solve by recursions does without: about
+    20 flops per node), by the usual count of 5 m log2(m) per
     complex FFT of m points: the n columns go two to a complex row; each row
     runs a forward and an inverse transform, each one m-point FFT (m = n, a
     power of two) or two through the chirp-z core (m = the power of two at
@@ -213,9 +210,6 @@ def bench_serve(args):
             log(f"saturated (prec {precision}): {sat:.3f} solves/s over {len(res)} requests")
             if profile:
                 out["profile"] = bhx.engine_profile(srv.engine)
-                # the engine's profile covers the warm-up requests too
-                out["served"] = [(r.request.tag.n, r.stats["iterations"])
-                                 for r in res_warm + res]
                 return out
             if timed:
                 rate = 0.8 * sat
@@ -275,23 +269,6 @@ def bench_serve(args):
                               "saturated phase again; bytes per launch summed over the "
                               "requests each launch worked on"}
     log(f"roofline: {PASS_KERNELS[dom]} {achieved:.1f} GB/s ({achieved / HBM_PEAK_GBS:.3f})")
-    # the column pass seen from the arithmetic side: chirp-z cores give it more
-    # flops per byte than the FP64 vector ridge (peak flops / peak bandwidth)
-    col_ms = prof["ms"][2]
-    col_flops = sum(it * column_pass_flops(n) for n, it in prof_out["served"])
-    col_bytes = 2 * 8 * prof["nodes"][2]
-    if col_ms > 0 and col_bytes > 0:
-        tflops = col_flops / (col_ms * 1e-3) / 1e12
-        roofline["column_pass_compute_view"] = {
-            "bound": "alu", "achieved": round(tflops, 2), "peak": FP64_VECTOR_PEAK_TFLOPS,
-            "unit": "TFLOP/s", "frac": round(tflops / FP64_VECTOR_PEAK_TFLOPS, 4),
-            "intensity_flop_per_byte": round(col_flops / col_bytes, 1),
-            "ridge_flop_per_byte": round(FP64_VECTOR_PEAK_TFLOPS * 1e12 / (HBM_PEAK_GBS * 1e9), 1),
-            "count": "5 m log2(m) flops per complex m-point FFT; per pair of columns a forward "
-                     "and an inverse transform, two FFTs each through a chirp-z core (m the "
-                     "power of two >= 2n - 1), one each for a power-of-two side (m = n); "
-                     "summed over the profiled requests' iterations"}
-        log(f"column pass: {tflops:.2f} TFLOP/s FP64, {col_flops / col_bytes:.1f} flop/B")
     out = {
         "metric": METRIC, "value": fp64["solves_per_s"], "unit": "solves/s", "n_gpus": 1,
         "steps": fp64["requests"], "warmup": len(sets["warm"]),
