@@ -45,8 +45,9 @@
  *     A Dirichlet axis of n nodes is transformed through a DFT of length
  *     2(n+1) (its odd extension) or, for 1366 <= n <= 2046, through a
  *     chirp-z transform of n+1 points; either must fit LDS like any
- *     transform: n <= 2047 in FP64 and FP32 (in three dimensions the y and z
- *     axes take n <= 1023 or n = 2047); otherwise BHX_ERR_ARG.
+ *     transform: n <= 2047 in FP64 and FP32, and in FP32 also n = 4095 (in
+ *     three dimensions the y and z axes take n <= 1023, n = 2047 or, in FP32,
+ *     n = 4095); otherwise BHX_ERR_ARG.
  */
 #ifndef BHX_H
 #define BHX_H

@@ -106,10 +106,10 @@ __host__ __device__ inline int col_rows(int n, int W) {
   return r;
 }
 // Kernel class of the column solve for such columns: 0 at most 8 rows a lane,
-// 1 at most 32, 2 more (FP32 only).
-inline int col_class(int n, int W) {
+// 1 at most 32, 2 more (FP32 only), 3 more on a Dirichlet axis (4095 nodes).
+inline int col_class(int n, int W, int bc) {
   const int r = col_rows(n, W);
-  return r <= 8 ? 0 : r <= 32 ? 1 : 2;
+  return r <= 8 ? 0 : r <= 32 ? 1 : bc == kDirichlet ? 3 : 2;
 }
 __host__ __device__ inline int col_stride(int n, int lc, int W) {
   const int s = (n + lc - 1) / lc * (lc > 1 ? lc + 1 : 1);

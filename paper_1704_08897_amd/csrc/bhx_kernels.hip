@@ -2321,9 +2321,16 @@ __global__ void __launch_bounds__(kColThreads, LONG ? 2 : 4)
         if constexpr (LONG > 0) {
           switch (lc) { BHX_COL(16) BHX_COL(32) }
         }
-        // FP32 axes of more than 2048 nodes (no Dirichlet axis is that long)
-        if constexpr (LONG > 1)
-          if (lc > 32) col_item<R, 64, 1, false, d3>(tile, B, I, c, zero);
+        // FP32 axes of more than 2048 nodes.  Of Dirichlet ones 4095 alone is
+        // taken (its odd extension has 8192 points, a power of two); its form
+        // has a class of its own, since beside it the compiler spills registers
+        // in the others (3000 x 3000 nodes, Neumann: 52 -> 56 us)
+        if constexpr (LONG > 1) {
+          if (lc > 32) {
+            if (LONG > 2 && odd) col_item<R, 64, 1, true, d3>(tile, B, I, c, zero);
+            else col_item<R, 64, 1, false, d3>(tile, B, I, c, zero);
+          }
+        }
         break;
     }
 #undef BHX_COL
@@ -3439,8 +3446,10 @@ static hipError_t launch_colsolve_pass(const Batch* B, int lng, int count_iter, 
     BHX_LAUNCH_T((k_colsolve<R, PASS, 0>), kColThreads, grid, lds, st, e0, e1, B, count_iter);
   else if (lng == 1 || sizeof(R) == 8)
     BHX_LAUNCH_T((k_colsolve<R, PASS, 1>), kColThreads, grid, lds, st, e0, e1, B, count_iter);
-  else
+  else if (lng == 2)
     BHX_LAUNCH_T((k_colsolve<float, PASS, 2>), kColThreads, grid, lds, st, e0, e1, B, count_iter);
+  else
+    BHX_LAUNCH_T((k_colsolve<float, PASS, 3>), kColThreads, grid, lds, st, e0, e1, B, count_iter);
   return hipGetLastError();
 }
 hipError_t launch_colsolve(const Batch* B, int prec, int pass, int lng, int count_iter, int grid,
@@ -3588,11 +3597,13 @@ hipError_t set_kernel_attributes() {
   set((const void*)k_colsolve<float, kPassC, 0>);
   set((const void*)k_colsolve<float, kPassC, 1>);
   set((const void*)k_colsolve<float, kPassC, 2>);
+  set((const void*)k_colsolve<float, kPassC, 3>);
   set((const void*)k_colsolve<double, kPassZ, 0>);
   set((const void*)k_colsolve<double, kPassZ, 1>);
   set((const void*)k_colsolve<float, kPassZ, 0>);
   set((const void*)k_colsolve<float, kPassZ, 1>);
   set((const void*)k_colsolve<float, kPassZ, 2>);
+  set((const void*)k_colsolve<float, kPassZ, 3>);
   set((const void*)k_ypass<double, kColYFwd, 0>);
   set((const void*)k_ypass<float, kColYFwd, 0>);
   set((const void*)k_ypass<double, kColYInv, 0>);

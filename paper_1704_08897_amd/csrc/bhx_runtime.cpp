@@ -924,10 +924,10 @@ int batch_grids(const PlanCache& plans, const BatchDesc& D, const Resolved& R, i
         buf_c = std::max(buf_c, (D.lay[i].Gc / 2) * row_slots(PY.m));
         tab_c = std::max(tab_c, table_slots(PY.n, PY.m, PY.bc, false));
         g.lds_z = std::max(g.lds_z, col_lds(D.inst[i].nz, D.lay[i].Gz, R.precision));
-        g.lng = std::max(g.lng, col_class(D.inst[i].nz, D.lay[i].Gz));
+        g.lng = std::max(g.lng, col_class(D.inst[i].nz, D.lay[i].Gz, D.inst[i].bcz));
       } else {
         g.lds_c = std::max(g.lds_c, col_lds(D.inst[i].ny, D.lay[i].Gc, R.precision));
-        g.lng = std::max(g.lng, col_class(D.inst[i].ny, D.lay[i].Gc));
+        g.lng = std::max(g.lng, col_class(D.inst[i].ny, D.lay[i].Gc, D.inst[i].bcy));
       }
     }
     g.tw_r = buf_r;

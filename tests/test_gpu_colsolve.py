@@ -75,3 +75,13 @@ def test_columns_3d_wide(handle, nz):
     """At least 4096 columns: the 16-lane items."""
     for rules in ((0, 1, 0), (1, 1, 1), (0, 0, 2), (2, 1, 1)):
         check(handle, (nz, 64, 65), rules, 0, 0.5)
+
+
+@pytest.mark.parametrize("shape,rules", [((4095, 24), (0, 2)), ((4095, 24), (1, 2)),
+                                         ((4095, 24), (2, 2)), ((24, 4095), (2, 0)),
+                                         ((4095, 5, 6), (0, 1, 2)), ((4095, 5, 6), (2, 2, 2)),
+                                         ((4, 4095, 6), (1, 2, 0)), ((6, 4, 4095), (2, 0, 1))])
+def test_longest_dirichlet_axis_fp32(handle, shape, rules):
+    """4095 nodes, the one FP32 Dirichlet length above 2047 (an odd extension of
+    8192 points): as the last axis, whose lanes hold 64 rows, and as the others."""
+    check(handle, shape, rules, 1, 0.3)
