@@ -85,3 +85,65 @@ def test_longest_dirichlet_axis_fp32(handle, shape, rules):
     """4095 nodes, the one FP32 Dirichlet length above 2047 (an odd extension of
     8192 points): as the last axis, whose lanes hold 64 rows, and as the others."""
     check(handle, shape, rules, 1, 0.3)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("ny", [4, 15, 16, 17, 31, 33, 63, 65, 127, 128, 129, 255, 257, 511, 512])
+def test_columns_2d_wide(handle, ny, prec):
+    """The 32-column items of shared launches (rows = -1) at the edges of their
+    16-lane segments.  The first iterate of the solve is a multiple of the
+    preconditioned right-hand side: compared by direction, at most twice the
+    operator's bound apart.  37 and 64 columns: a partly and a fully used item."""
+    for nx, bx in ((37, 1), (64, 0), (65, 2)):
+        for by in (0, 1, 2):
+            rng = np.random.default_rng(ny + 10 * nx + by)
+            phi = -(rng.random((ny, nx)) - 0.7)
+            F = rng.normal(size=(ny, nx))
+            known = O.known_mask(phi)
+            b = np.zeros((ny, nx))
+            b[~known] = O.rhs(F, known, bx, by)
+            z = O.spectral_preconditioner(b, known, bx, by)[~known]
+            G = dev(F)
+            s, st = bhx.extend_ex(handle, dev(phi), G, bc=bhx.BC(bx, by), tol=1e-14,
+                                  opts=bhx.default_opts(maxit=1, rows=-1, precision=prec))
+            assert s == bhx.NOT_CONVERGED and st.iterations == 1
+            x = G.cpu().numpy()[~known]
+            d = x / np.linalg.norm(x) - z / np.linalg.norm(z)
+            assert np.linalg.norm(d) <= 2 * BOUND[prec], (nx, bx, by)
+
+
+@pytest.mark.parametrize("nz", [4, 17, 128, 129, 512])
+def test_columns_3d_wide_fp32(handle, nz):
+    for rules in ((0, 1, 0), (1, 1, 1), (0, 0, 2), (2, 1, 1)):
+        check(handle, (nz, 64, 65), rules, 1, 0.5)
+
+
+@pytest.mark.parametrize("prec,by", [(0, 0), (0, 1), (0, 2), (1, 0), (1, 1), (1, 2)])
+@pytest.mark.parametrize("rows", [0, -1])
+def test_batch_across_column_classes(handle, rows, prec, by, monkeypatch):
+    """An instance alone and in a batch whose longest column takes the launch to
+    another kernel class (edges at 512 nodes of 8-column items, 128 of 32-column
+    ones, 2048 in FP32): the same bits."""
+    monkeypatch.setenv("BHX_SHAPE_KERNELS", "0")
+    sides = [(45, 60), (75, 128), (90, 129), (50, 512), (41, 513), (33, 1300)]
+    if prec == 1:
+        sides.append((20, 4095 if by == 2 else 3000))
+    ins = []
+    for nx, ny in sides:
+        y, x = np.meshgrid(np.linspace(-1, 1, ny), np.linspace(-1, 1, nx), indexing="ij")
+        ins.append((dev(np.hypot(x, y) - 0.5), dev(np.cos(2 * x) + np.sin(y))))
+    o = bhx.default_opts(maxit=24, rows=rows, precision=prec)
+    bc = bhx.BC(0, by)
+    alone = []
+    for phi, F in ins:
+        G = F.clone()
+        s, _ = bhx.extend_ex(handle, phi, G, h=0.01, bc=bc, tol=1e-14, opts=o)
+        assert s == bhx.NOT_CONVERGED
+        alone.append(G)
+    outs = [F.clone() for _, F in ins]
+    k = len(ins)
+    s, _ = bhx.extend_batched(handle, [p for p, _ in ins], outs, [0.01] * k, [bc] * k,
+                              [1e-14] * k, opts=o)
+    assert s == bhx.NOT_CONVERGED
+    for a, b in zip(alone, outs):
+        assert torch.equal(a, b)
