@@ -17,9 +17,8 @@ namespace bhx {
 namespace {
 
 constexpr size_t kScratchBytes = (size_t)BHX_NOALLOC_SCRATCH_BYTES;
-// The limit counts tiles of 32 rows.  The halves of a tile (kTileY rows) keep
-// their partial sums and list entries past it: 28 bytes a tile, fewer than 2600
-// tiles for what fits.
+// What the layout in use takes past the limit's count (noalloc_limit_bytes): at most
+// 94 KiB over every size that fits.
 constexpr size_t kScratchSlack = 128 << 10;
 constexpr int kMaxDevices = 64;
 
@@ -33,8 +32,48 @@ std::mutex g_call_mu[kMaxDevices];
 
 size_t up256(size_t x) { return (x + 255) / 256 * 256; }
 
-
 }  // namespace
+
+// Bytes of scratch that the limit counts for an instance.  Which sizes fit is
+// part of the interface and must not move with a kernel's tiles, work items or
+// tables, so this is a fixed layout: stencil tiles of 64 x 32 nodes,
+// transforms by full_core_length, and work items of the fullest row and column
+// groups those leave room for.  `nc`, `nr`: the complex and real table entries
+// in use.
+size_t noalloc_limit_bytes(const InstSpec& S, const Resolved& R, const PlanCache& plans,
+                           const BatchDesc& D, size_t nc, size_t nr) {
+  if (D.dense[0]) return 0;              // at most kDenseMax nodes a side: always fits
+  const int cap = R.precision == 0 ? 4 : 8, csize = R.precision == 0 ? 16 : 8;
+  auto groups = [&](int n, int bc, long lines) {
+    int nf;
+    const int m = full_core_length(n, bc, &nf);
+    int r = std::min(std::min(cap, kLdsBytes / (row_slots(m) * csize)),
+                     (kThreads * kMaxPairs) / (n / 2 + 1));
+    if (R.sched.rows_cap > 0) r = std::min(r, R.sched.rows_cap);
+    if (R.sched.rows_cap == 0)
+      while (r > 1 && (lines + 2 * r - 1) / (2 * r) < kTargetItems) --r;
+    return (size_t)(lines + 2 * r - 1) / (2 * r);
+  };
+  const size_t nS = (size_t)((S.nx + 63) / 64) * ((S.ny + 31) / 32);
+  const size_t nR = groups(S.nx, S.bcx, S.ny), nC = groups(S.ny, S.bcy, S.nx);
+  const int n_plans = D.px[0] == D.py[0] ? 1 : 2;
+  for (int a = 0; a < n_plans; ++a) {
+    const AxisPlan& P = plans.plan(a == 0 ? D.px[0] : D.py[0]);
+    int nf;
+    const int m = full_core_length(P.n, P.bc, &nf);
+    nc += m / 2 + (m != nf ? nf + m : 0);
+    nc -= P.m / 2 + (P.bluestein ? P.nf + P.m : 0);
+  }
+  const size_t N = (size_t)S.nx * S.ny;
+  return up256(sizeof(Batch)) + up256(sizeof(Inst)) + up256(nS * sizeof(int)) +
+         up256(nR * sizeof(int)) + up256(nC * sizeof(int)) + 3 * up256(sizeof(int)) +
+         up256(n_plans * sizeof(AxisPlan)) + up256(nc * sizeof(double2)) +
+         up256(nc * sizeof(float2)) + up256(nr * sizeof(double)) + up256(nr * sizeof(float)) +
+         up256(sizeof(int)) + ctl_region_bytes(1) + up256(N) +
+         up256(5 * vec_stride(S.nx, S.ny) * sizeof(double)) +
+         up256(N * (R.precision == 0 ? sizeof(double) : sizeof(float))) +
+         up256((size_t)PartLayout((int)nS, (int)nR).total() * sizeof(double)) + up256(sizeof(Ctl));
+}
 
 int noalloc_scratch(int device, void** ptr, size_t* bytes) {
   if (device < 0 || device >= kMaxDevices) return BHX_ERR_ARG;
@@ -116,14 +155,12 @@ int solve_noalloc(bhx_handle* hd, const InstSpec& spec, const Resolved& R, hipSt
   const size_t o_rf = o;    o = up256(o + rf.size() * sizeof(float));
   const size_t o_flag = o;  o = up256(o + sizeof(int));
   const size_t o_ws = o;    o = up256(o + D.ws_bytes);
-  const size_t halves = (size_t)D.inst[0].tiles_x *
-                        (D.inst[0].tiles_y - (spec.ny + 2 * kTileY - 1) / (2 * kTileY));
-  const size_t past = halves * (3 * sizeof(double) + sizeof(int));
-  if (o > cap + std::min(past, kScratchSlack)) {
+  const size_t counted = noalloc_limit_bytes(spec, R, plans, D, cd.size(), rd.size());
+  if (counted > cap || o > cap + kScratchSlack) {
     char msg[200];
     snprintf(msg, sizeof(msg),
              "bhx_extend_noalloc: %dx%d needs %zu bytes of scratch, the limit is %zu", spec.nx,
-             spec.ny, o, cap);
+             spec.ny, std::max(counted, o), cap);
     set_last_message(msg);
     return BHX_ERR_ARG;
   }

@@ -115,13 +115,16 @@ int fft_length(int n, int bc) {
   return dst_chirp(n, bc) ? n + 1 : 2 * (n + 1);
 }
 
+int full_core_length(int n, int bc, int* nf) {
+  *nf = bc != kDirichlet ? n : dst_long(n, bc) ? n + 1 : 2 * (n + 1);
+  return is_pow2(*nf) ? *nf : pow2_at_least(2 * *nf - 1);
+}
+
 bool length_supported(int n, int bc, int prec) {
   if (n < 4) return false;
   const int csize = prec == 0 ? 16 : 8;
-  // The range is that of the full convolution (2 nf - 1 points; n + 1 point
-  // chirp-z from 1024 nodes on), whose core is never shorter than core_length.
-  const int nf = bc != kDirichlet ? n : dst_long(n, bc) ? n + 1 : 2 * (n + 1);
-  const int m = is_pow2(nf) ? nf : pow2_at_least(2 * nf - 1);
+  int nf;
+  const int m = full_core_length(n, bc, &nf);
   if ((long)row_slots(m) * csize > kLdsBytes) return false;        // one packed row must fit
   if ((long)(row_slots(m) + table_slots(n, m, bc, true)) * csize > kLdsDynMax) return false;
   if ((n / 2 + 1) > kThreads * kMaxPairs) return false;

@@ -85,10 +85,14 @@ inline bool make_layout(int nx, int ny, int prec, int mx, int my, int rows_cap, 
 int col_lds(int n, int W, int prec);
 // Core FFT length of the transform of an axis (power of two, or Bluestein).
 int core_length(int n, int bc);
+// The core and the DFT length nf by which the interface's limits count an axis:
+// the full convolution of 2 nf - 1 points, with the n + 1 point chirp-z form
+// from 1024 Dirichlet nodes on.  Never shorter than core_length.
+int full_core_length(int n, int bc, int* nf);
 // Spacing of the float64 workspace vectors (elements), 256-byte aligned.
 size_t vec_stride(int nx, int ny);
-// Largest supported transform length for a precision (0 fp64, 1 fp32).
-bool length_supported(int n, int prec);
+// Whether an axis' transform fits, for a precision (0 fp64, 1 fp32).
+bool length_supported(int n, int bc, int prec);
 
 // Launch schedule: packed rows per transform item (0 = policy), persistent
 // blocks per CU of the stencil / row / column passes (occ_r = 0: row_occupancy).

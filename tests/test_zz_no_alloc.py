@@ -85,3 +85,26 @@ def test_noalloc_options_and_limits(handle):
     s, _ = bhx.extend_noalloc(handle, dev(p.phi), dev(p.F), bc=p.bc, h=p.h, tol=1e-8,
                               opts=bhx.default_opts(autotune=1))
     assert s == bhx.ERR_ARG
+
+
+@pytest.mark.parametrize("nx,ny,bx,by,prec,rows,fits", [
+    (1024, 1327, 2, 2, 0, 0, True), (1365, 997, 2, 0, 0, 0, True),
+    (1100, 1345, 0, 2, 1, 0, True), (1024, 1445, 2, 1, 1, 0, True),
+    (700, 1944, 0, 0, 0, -1, True),
+    (1200, 1133, 0, 0, 0, 0, False), (2000, 680, 0, 2, 0, 0, False),
+    (512, 2881, 2, 0, 1, 0, False)])
+def test_sizes_at_the_limit(handle, nx, ny, bx, by, prec, rows, fits):
+    """Sizes within 0.1% of the limit: it counts a layout of its own, so they
+    are taken or refused whatever tables and work items the kernels use."""
+    p = star(nx, ny, bx, by, 4)
+    o = bhx.default_opts(maxit=2, precision=prec, rows=rows)
+    Fa = dev(p.F)
+    s, _ = bhx.extend_noalloc(handle, dev(p.phi), Fa, bc=p.bc, h=p.h, tol=1e-12, opts=o)
+    if not fits:
+        assert s == bhx.ERR_ARG and "limit" in bhx.last_error()
+        assert torch.equal(Fa, dev(p.F))
+        return
+    assert s == bhx.NOT_CONVERGED
+    Fb = dev(p.F)
+    bhx.extend_ex(handle, dev(p.phi), Fb, bc=p.bc, h=p.h, tol=1e-12, opts=o)
+    assert torch.equal(Fa, Fb)
