@@ -1,5 +1,6 @@
 // C-ABI entry points (include/bhx.h): argument validation on the host, then
 // the batched solver.  Nothing is thrown across this boundary.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -179,8 +180,13 @@ size_t bhx_workspace_bytes(int nx, int ny, int bc, const bhx_opts* o) {
   const Resolved R = bhx::resolve_opts(o);
   static const double dummy = 0;
   if (bhx::validate(&dummy, (double*)&dummy, nx, ny, 1.0, bc, 0.5, R) != BHX_OK) return 0;
-  return bhx::instance_bytes(nx, ny, bc & 15, (bc >> 4) & 15, R.precision) + sizeof(bhx::Inst) +
-         64;
+  // the most that a solve, an engine or the given rows take (short work items
+  // have more partial sums)
+  size_t most = 0;
+  for (int rows : {0, -1, R.sched.rows_cap})
+    most = std::max(most,
+                    bhx::instance_bytes(nx, ny, bc & 15, (bc >> 4) & 15, R.precision, rows));
+  return most == 0 ? 0 : most + sizeof(bhx::Inst) + 64;
 }
 
 int bhx_debug_apply(bhx_handle* hd, int op, const double* phi, const double* in, double* out,

@@ -151,6 +151,28 @@ def test_admission_by_slots_and_budget():
         srv.close()
 
 
+@pytest.mark.parametrize("nx,ny,prec,rows", [(2048, 2048, 0, 0), (1798, 2047, 1, 0),
+                                             (1151, 3799, 1, 0), (621, 2354, 1, 1), (64, 64, 0, 0)])
+def test_budget_of_workspace_bytes_fits_the_request(nx, ny, prec, rows):
+    """bhx_workspace_bytes covers the engine's layout of a request, whose work
+    items (and with them the partial sums) are not those of a solve alone."""
+    o = bhx.default_opts(precision=prec, rows=rows)
+    need = max(bhx.workspace_bytes(nx, ny, 0, o), 1 << 20)
+    y, x = np.meshgrid(np.linspace(-1, 1, ny), np.linspace(-1, 1, nx), indexing="ij")
+    srv = Server(0, hbm_budget=need, max_slots=1, precision=prec, rows=rows, maxit=2, chunk=2)
+    try:
+        req = Request(dev(np.hypot(x, y) - 0.5), dev(x + y), 0, 1.0, 1e-10)
+        s, _ = bhx.engine_submit(srv.engine, req.phi, req.F, nx, ny, 1.0, 0, 1e-10)
+        assert s == bhx.OK
+        t0 = time.time()
+        while srv.inflight() and time.time() - t0 < 30:
+            srv.poll()
+            time.sleep(1e-3)
+        assert srv.inflight() == 0
+    finally:
+        srv.close()
+
+
 def test_error_statuses_per_request():
     n = 32
     F = np.random.default_rng(0).normal(size=(n, n))
