@@ -29,7 +29,8 @@ constexpr int kThreads = 256;          // threads per workgroup, every kernel
 // helps is tiles in flight: 16 rows give twice the blocks of 32, with four
 // instead of three on a CU.  Stencil pass with 32 -> 16 rows: 64x64 7.5 -> 6.4
 // us, 450x450 9.4 -> 7.7, 1231x877 18.4 -> 16.0, eight served requests 35.8 ->
-// 23.4; 1024x1024 of which one tile in eight has unknown nodes 9.5 -> 10.7.
+// 23.4; 1024x1024 of which one tile in eight has unknown nodes 9.5 -> 10.7 (with
+// the tiles spread over the CUs, stencil_block(), 9.9).
 constexpr int kTileX = 64;
 constexpr int kTileY = 16;
 constexpr int kTileX3 = 16;            // stencil tile (nodes), three dimensions
