@@ -1369,6 +1369,38 @@ static unsigned long long batch_signature(int n, const InstSpec* specs, const Re
   return h;
 }
 
+// Candidate schedules of the autotuner: first the built-in policy, so that
+// tuning never ends slower than it; its row grouping and occupancies are no
+// combination of those below (64 mixed instances of 64 to 512 nodes a side,
+// 48 iterations: 10.8 ms by the policy, 11.1 by the best of the others).
+// `eligible`: some instance has a dense form.
+std::vector<Schedule> autotune_candidates(const Resolved& R, bool eligible, int trial_iters) {
+  std::vector<Schedule> cands;
+  const int t_opt = R.transform;
+  auto add = [&](int rows, int occ_r, int occ_c, int transform, int occ_d) {
+    Schedule s;
+    s.rows_cap = rows;
+    s.occ_r = occ_r;
+    s.occ_c = occ_c;
+    s.chunk = trial_iters;
+    s.transform = transform;
+    s.occ_d = occ_d;
+    cands.push_back(s);
+  };
+  const Schedule d;
+  add(d.rows_cap, d.occ_r, d.occ_c, t_opt, d.occ_d);
+  // the FFT family under every grouping and occupancy (the option's
+  // transform choice when it fixes one)
+  for (int rows : {1, 2, 4})
+    for (int occ : {1, 2, 4}) add(rows, occ, occ, t_opt == 0 ? 1 : t_opt, d.occ_d);
+  // with the transform left to the library: the built-in choice and dense
+  // wherever the axes allow, at one or two dense blocks per CU
+  if (t_opt == 0 && eligible && R.precond)
+    for (int t : {0, 2})
+      for (int occ_d : {1, 2}) add(2, 2, 2, t, occ_d);
+  return cands;
+}
+
 // Project autotuner: time short trial solves (a fixed number of iterations
 // in one graph) of this batch's shape under candidate schedules and keep the
 // fastest.  A trial writes F only at unknown nodes, which a cold solve
@@ -1377,38 +1409,10 @@ static unsigned long long batch_signature(int n, const InstSpec* specs, const Re
 static int autotune_schedule(bhx_handle* hd, int n, const InstSpec* specs, const Resolved& R,
                              hipStream_t stream, Schedule* best) {
   const int trial_iters = 24;
-  std::vector<Schedule> cands;
-  // the FFT family under every grouping and occupancy (the option's
-  // transform choice when it fixes one)
-  const int t_opt = R.transform;
-  for (int rows : {1, 2, 4})
-    for (int occ : {1, 2, 4}) {
-      Schedule s;
-      s.rows_cap = rows;
-      s.occ_r = occ;
-      s.occ_c = occ;
-      s.occ_s = 8;
-      s.chunk = trial_iters;
-      s.transform = t_opt == 0 ? 1 : t_opt;
-      cands.push_back(s);
-    }
-  // with the transform left to the library: the built-in choice and dense
-  // wherever the axes allow, at one or two dense blocks per CU
   bool eligible = false;
   for (int i = 0; i < n; ++i)
     eligible |= specs[i].dim == 2 && specs[i].nx <= kDenseMax && specs[i].ny <= kDenseMax;
-  if (t_opt == 0 && eligible && R.precond)
-    for (int t : {0, 2})
-      for (int occ_d : {1, 2}) {
-        Schedule s;
-        s.rows_cap = 2;
-        s.occ_r = s.occ_c = 2;
-        s.occ_s = 8;
-        s.chunk = trial_iters;
-        s.transform = t;
-        s.occ_d = occ_d;
-        cands.push_back(s);
-      }
+  const std::vector<Schedule> cands = autotune_candidates(R, eligible, trial_iters);
   double best_t = 1e30;
   std::vector<bhx_stats> st(n);
   for (const Schedule& s : cands) {

@@ -113,6 +113,8 @@ struct Resolved {           // options after defaults
   Schedule sched;
 };
 Resolved resolve_opts(const bhx_opts* o);
+// Schedules that the autotuner times, the built-in policy first.
+std::vector<Schedule> autotune_candidates(const Resolved& R, bool eligible, int trial_iters);
 
 struct Grids {
   int s, r, c;             // persistent grid sizes of the stencil, row and column passes
