@@ -102,8 +102,10 @@ def pass_bytes(p, n_unknown, N, prec):
 
 
 def kernel_source_hash():
-    src = os.path.join(ROOT, "paper_1704_08897_amd", "csrc", "bhx_kernels.hip")
-    return hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
+    csrc = os.path.join(ROOT, "paper_1704_08897_amd", "csrc")
+    src = b"".join(open(os.path.join(csrc, f), "rb").read()
+                   for f in ("bhx_kernels.hip", "bhx_colsolve.h", "bhx_device.h"))
+    return hashlib.sha256(src).hexdigest()[:16]
 
 
 def load_traffic(kernel, wl):

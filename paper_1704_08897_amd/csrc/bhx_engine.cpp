@@ -228,7 +228,7 @@ Grids engine_grids(bhx_engine* E, const std::vector<Req*>& reqs) {
     plan_family(PX, q->inst.G / 2, &g.shape_r);  // plan-table kernel family
     buf_r = std::max(buf_r, (q->inst.G / 2) * row_slots(PX.m));
     lds_c = std::max(lds_c, col_lds(q->inst.ny, q->inst.Gc, E->R.precision));
-    g.lng = std::max(g.lng, col_class(q->inst.ny, q->inst.Gc, q->inst.bcy));
+    g.cls.add(col_class(q->inst.ny, q->inst.Gc, q->inst.bcy));
   }
   // the engine runs the plan-table kernels, which read their tables from
   // global memory: LDS for the packed rows alone, rounded up to 4 KiB steps

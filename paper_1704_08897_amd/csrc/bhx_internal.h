@@ -112,6 +112,17 @@ inline int col_class(int n, int W, int bc) {
   const int r = col_rows(n, W);
   return r <= 8 ? 0 : r <= 32 ? 1 : bc == kDirichlet ? 3 : 2;
 }
+// The classes of a launch's columns: the largest below 3 and whether class 3 is
+// among them.
+struct ColClasses {
+  int lng = 0;
+  bool odd64 = false;
+  void add(int c) {
+    if (c == 3) odd64 = true;
+    else lng = c > lng ? c : lng;
+  }
+  bool operator==(const ColClasses& o) const { return lng == o.lng && odd64 == o.odd64; }
+};
 __host__ __device__ inline int col_stride(int n, int lc, int W) {
   const int s = (n + lc - 1) / lc * (lc > 1 ? lc + 1 : 1);
   return W == kColWide ? s | 1 : (s + 27) / 32 * 32 + 4;
@@ -339,10 +350,14 @@ hipError_t launch_rowfwd(const Batch* B, int prec, int shape, int update, int gr
                          int twoff, int lpar, hipStream_t st, hipEvent_t e0 = nullptr,
                          hipEvent_t e1 = nullptr);
 // Column solve along the last axis: `pass` kPassC (two dimensions) or kPassZ.
-// `lng`: the largest col_class of the launch.
-hipError_t launch_colsolve(const Batch* B, int prec, int pass, int lng, int count_iter, int grid,
-                           int lds, hipStream_t st, hipEvent_t e0 = nullptr,
+// `cls`: the launch's column classes.
+hipError_t launch_colsolve(const Batch* B, int prec, int pass, ColClasses cls, int count_iter,
+                           int grid, int lds, hipStream_t st, hipEvent_t e0 = nullptr,
                            hipEvent_t e1 = nullptr);
+// Its class-3 columns, after the others (e1: recorded at its end).
+hipError_t launch_colsolve_odd64(const Batch* B, int pass, int grid, int lds, hipStream_t st,
+                                 hipEvent_t e1);
+hipError_t set_colsolve_odd64_attributes();
 // y transform of three dimensions (`kind`: ColKind).
 hipError_t launch_ypass(const Batch* B, int prec, int shape, int kind, int grid, int lds,
                         int twoff, hipStream_t st);

@@ -530,13 +530,13 @@ namespace {
 hipError_t launch_columns(const Batch* B, const Resolved& R, const Grids& g, int count_iter,
                           hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
   if (g.dim == 2)
-    return launch_colsolve(B, R.precision, kPassC, g.lng, count_iter, g.c, g.lds_c, st, e0, e1);
+    return launch_colsolve(B, R.precision, kPassC, g.cls, count_iter, g.c, g.lds_c, st, e0, e1);
   hipError_t e;
   if (e0 && (e = hipEventRecord(e0, st)) != hipSuccess) return e;
   if ((e = launch_ypass(B, R.precision, g.shape_c, kColYFwd, g.c, g.lds_c, g.tw_c, st)) !=
       hipSuccess)
     return e;
-  if ((e = launch_colsolve(B, R.precision, kPassZ, g.lng, count_iter, g.z, g.lds_z, st)) !=
+  if ((e = launch_colsolve(B, R.precision, kPassZ, g.cls, count_iter, g.z, g.lds_z, st)) !=
       hipSuccess)
     return e;
   if ((e = launch_ypass(B, R.precision, g.shape_c, kColYInv, g.c, g.lds_c, g.tw_c, st)) !=
@@ -677,7 +677,7 @@ hipError_t run_chunk(bhx_handle* hd, const Batch* B, int n_inst, const Resolved&
         gr.prec == R.precision && gr.chunk == R.chunk &&
         gr.precond == R.precond && gr.gs == g.s && gr.gr == g.r && gr.gc == g.c &&
         gr.lds_r == g.lds_r && gr.tw_r == g.tw_r && gr.lds_c == g.lds_c && gr.tw_c == g.tw_c &&
-        gr.dim == g.dim && gr.gz == g.z && gr.lds_z == g.lds_z && gr.lng == g.lng &&
+        gr.dim == g.dim && gr.gz == g.z && gr.lds_z == g.lds_z && gr.cls == g.cls &&
         gr.shape_r == g.shape_r && gr.shape_c == g.shape_c && gr.fft == g.fft && gr.dense == g.dense &&
         gr.rd == g.rd && gr.cd == g.cd && gr.lds_rd == g.lds_rd && gr.tab_rd == g.tab_rd &&
         gr.lds_cd == g.lds_cd && gr.tab_cd == g.tab_cd &&
@@ -693,7 +693,7 @@ hipError_t run_chunk(bhx_handle* hd, const Batch* B, int n_inst, const Resolved&
   G.reduce = g.reduce;
   G.gs = g.s; G.gr = g.r; G.gc = g.c; G.profile = R.profile;
   G.lds_r = g.lds_r; G.tw_r = g.tw_r; G.lds_c = g.lds_c; G.tw_c = g.tw_c;
-  G.dim = g.dim; G.gz = g.z; G.lds_z = g.lds_z; G.lng = g.lng;
+  G.dim = g.dim; G.gz = g.z; G.lds_z = g.lds_z; G.cls = g.cls;
   G.shape_r = g.shape_r; G.shape_c = g.shape_c;
   G.fft = g.fft; G.dense = g.dense; G.rd = g.rd; G.cd = g.cd;
   G.lds_rd = g.lds_rd; G.tab_rd = g.tab_rd; G.lds_cd = g.lds_cd; G.tab_cd = g.tab_cd;
@@ -927,10 +927,10 @@ int batch_grids(const PlanCache& plans, const BatchDesc& D, const Resolved& R, i
         buf_c = std::max(buf_c, (D.lay[i].Gc / 2) * row_slots(PY.m));
         tab_c = std::max(tab_c, table_slots(PY.n, PY.m, PY.bc, false));
         g.lds_z = std::max(g.lds_z, col_lds(D.inst[i].nz, D.lay[i].Gz, R.precision));
-        g.lng = std::max(g.lng, col_class(D.inst[i].nz, D.lay[i].Gz, D.inst[i].bcz));
+        g.cls.add(col_class(D.inst[i].nz, D.lay[i].Gz, D.inst[i].bcz));
       } else {
         g.lds_c = std::max(g.lds_c, col_lds(D.inst[i].ny, D.lay[i].Gc, R.precision));
-        g.lng = std::max(g.lng, col_class(D.inst[i].ny, D.lay[i].Gc, D.inst[i].bcy));
+        g.cls.add(col_class(D.inst[i].ny, D.lay[i].Gc, D.inst[i].bcy));
       }
     }
     g.tw_r = buf_r;

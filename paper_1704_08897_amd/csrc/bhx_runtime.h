@@ -122,7 +122,7 @@ struct Grids {
   int lds_c, tw_c;         // column solve (two dimensions) or y transforms (three)
   int dim = 2;             // 3: y transform, column solve along z, y transform
   int z = 0, lds_z = 0;    // column solve along z (three dimensions)
-  int lng = 0;             // column solve: the largest col_class
+  ColClasses cls;          // column solve
   int count = 0;           // instances of the batch
   int reduce = 0;          // 1: some instance has Inst::reduce (k_reduce launches)
   int shape_r = 0, shape_c = 0;   // compile-time shapes of the passes (shape_key)
@@ -170,7 +170,8 @@ struct Graph {
   int count = 0;
   int prec = -1, chunk = 0, precond = -1, gs = 0, gr = 0, gc = 0, profile = 0;
   int lds_r = 0, tw_r = 0, lds_c = 0, tw_c = 0;
-  int dim = 2, gz = 0, lds_z = 0, lng = 0, reduce = 0, shape_r = 0, shape_c = 0;
+  int dim = 2, gz = 0, lds_z = 0, reduce = 0, shape_r = 0, shape_c = 0;
+  ColClasses cls;
   int fft = 1, dense = 0, rd = 0, cd = 0, lds_rd = 0, tab_rd = 0, lds_cd = 0, tab_cd = 0;
   std::vector<hipEvent_t> ev;   // [pass][iteration][start, end] when profiling
 };

@@ -147,3 +147,19 @@ def test_batch_across_column_classes(handle, rows, prec, by, monkeypatch):
     assert s == bhx.NOT_CONVERGED
     for a, b in zip(alone, outs):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("sides", [[(20, 4095)], [(20, 4095), (45, 60)], [(45, 60), (33, 1300)]])
+def test_profiled_launches_across_column_classes(handle, sides):
+    """The column pass of a 4095-node FP32 Dirichlet axis is a launch beside the
+    other columns': the profile counts and times the two as one pass."""
+    ins = [(dev(np.hypot(*np.meshgrid(np.linspace(-1, 1, ny), np.linspace(-1, 1, nx),
+                                      indexing="ij")) - 0.5), dev(np.ones((ny, nx))))
+           for nx, ny in sides]
+    k = len(ins)
+    o = bhx.default_opts(maxit=8, chunk=8, precision=1, profile=4)
+    s, sts = bhx.extend_batched(handle, [p for p, _ in ins], [F for _, F in ins], [0.01] * k,
+                                [bhx.BC(0, 2)] * k, [1e-14] * k, opts=o)
+    assert s == bhx.NOT_CONVERGED
+    assert sts[0].pass_launches[2] == 8 and sts[0].pass_ms[2] > 0
+    assert all(st.iterations == 8 for st in sts)
