@@ -112,8 +112,10 @@ typedef struct {
   int rows;         /* packed complex rows (two grid rows each) per transform work
                          item; 0 = automatic (autotuner or built-in policy: as many as
                          fit, fewer while the instance alone supplies under two items
-                         per CU); -1 = as many as fit (the engine's default, whose
-                         launches are shared by many requests)                        */
+                         per CU); -1 = the engine's default, for launches shared by
+                         many requests: as many as fit in fewer than 4096 points, and
+                         wider items of the column solve.  The last axis is solved
+                         without a transform: a positive value leaves it alone.       */
   int occupancy;    /* persistent blocks per CU of the transform passes; 0 = auto   */
   int autotune;     /* 1 = choose the launch schedule (packed rows per transform work
                          item, persistent-grid occupancy per pass, iterations per

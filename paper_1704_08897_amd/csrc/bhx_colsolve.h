@@ -33,8 +33,8 @@ namespace bhx {
 // bytes and about 20 operations per node in FP64).  The transforms it replaces
 // cost two FFTs per column, four of twice the length where Bluestein runs.  Per
 // launch, transforms -> recursions: 1024^2 12.1 -> 10.7 us, 2048^2 32.2 -> 17.9
-// (64 MB, 3.7 TB/s), 450^2 19.5 -> 7.3, 1231x877 69.2 -> 12.6 (17 MB, 1.4 TB/s),
-// 40 mixed instances 82.4 -> 13.2, 128^3 along z 21.0 -> 12.9.
+// (64 MB to load and store), 450^2 19.5 -> 7.3, 1231x877 69.2 -> 12.6 (17 MB), 40
+// mixed instances 82.4 -> 13.2, 128^3 along z 21.0 -> 12.9.
 // Relative to the spectral form its rounding is smaller in the energy norm
 // that conjugate gradients work in (about 1e-11 against 1e-10 at 2048 nodes
 // and the smallest lambda).

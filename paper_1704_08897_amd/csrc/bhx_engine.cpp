@@ -199,8 +199,8 @@ int upload_batch(bhx_engine* E, DevBatch& db, const std::vector<Req*>& reqs, hip
 }
 
 // Packed rows per transform work item of the engine's requests: the
-// caller's bhx_opts.rows, else the fullest items (-1): every launch is
-// shared with other requests, so none has to fill the GPU alone.  A request
+// caller's bhx_opts.rows, else those of shared launches (-1): every launch holds
+// other requests too, so none has to fill the GPU alone.  A request
 // equals its solo solve with the same bhx_opts.rows bit for bit.
 int engine_rows(const bhx_engine* E) {
   return E->R.sched.rows_cap != 0 ? E->R.sched.rows_cap : -1;

@@ -30,7 +30,7 @@ constexpr int kThreads = 256;          // threads per workgroup, every kernel
 // instead of three on a CU.  Stencil pass with 32 -> 16 rows: 64x64 7.5 -> 6.4
 // us, 450x450 9.4 -> 7.7, 1231x877 18.4 -> 16.0, eight served requests 35.8 ->
 // 23.4; 1024x1024 of which one tile in eight has unknown nodes 9.5 -> 10.7 (with
-// the tiles spread over the CUs, stencil_block(), 9.9).
+// the tiles spread over the CUs, stencil_block(), 9.6).
 constexpr int kTileX = 64;
 constexpr int kTileY = 16;
 constexpr int kTileX3 = 16;            // stencil tile (nodes), three dimensions
@@ -45,9 +45,17 @@ constexpr int kColThreads = 512;       // threads of the column solve
 constexpr int kColWaves = kColThreads / 64;
 constexpr int kColWide = 4 * kColWaves;   // columns of its wide items (16 lanes a column),
                                        // else kColWaves (64 lanes)
-// Wide items need an axis whose 32 columns fit LDS in FP64 beside a second block,
-// and enough columns to give every CU a block; in two dimensions one instance
-// has fewer (128 items of 32 columns leave half the CUs idle).
+// Wide items need an axis whose 32 columns fit the LDS of a block in FP64 (135 KB
+// at 512 nodes; two blocks fit a CU up to 288) and, in a launch of one instance,
+// enough columns to give every CU a block; in two dimensions one instance has
+// fewer (128 items of 32 columns leave half the CUs idle).  Shared launches take
+// them up to 512 nodes whatever the number of columns.  Past 128 nodes they
+// are of class 1, where 8 columns an item are class 0 up to 512 (col_class).
+// Column pass in the serving engine, FP64, this limit | 128: 4 requests of 64-128
+// nodes a side 5.5 | 5.5 us (8 columns throughout 5.9), 64 of them 9.9 | 9.9
+// (12.1), 8 of 128-256 15.4 | 9.4, 8 of 256-512 25.8 | 13.9, 64 of 129-512 39.6 |
+// 34.7, 8 of 128-800 22.2 | 15.7, 16 of 128-2048 55.8 | 55.3, 6 of 128-2048 30.5 |
+// 38.9: 128 would be the better limit but for few requests beside long ones.
 constexpr int kColWideMax = 512;       // longest axis of wide items
 constexpr int kColWideMin = 4096;      // columns one instance needs for wide items
 constexpr int kTargetItems = 512;      // row/column items one instance should supply
@@ -81,8 +89,6 @@ __host__ __device__ inline int stage_twiddles(int logm) {
   for (int h = (logm & 1) ? 2 : 1; h < (1 << logm); h <<= 2) t += h;
   return t;
 }
-// Work lists: stencil tiles, row groups (x rows), column groups (y pencils of
-// the transposed buffer) and, in three dimensions, z-pencil groups.
 // Spectral pairs (k, partner k) of a transform of n nodes: (k, n-k) mod n
 // for k <= n/2; DST-I (k, n-1-k) for k < (n+1)/2.
 __host__ __device__ inline int plan_pairs(int n, int bc) {

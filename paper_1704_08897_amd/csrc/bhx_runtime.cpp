@@ -162,6 +162,8 @@ bool make_layout(int nx, int ny, int nz, int prec, int mx, int my, int mz, int r
   const int rx = rows_for(nx, mx, nrows, rows_cap);
   // y pencils are strided: wider groups give longer contiguous runs
   const int ry = rows_for(ny, my, (long)nx * nz, d3 ? kMaxGc / 2 : rows_cap);
+  // z pencils: no transform runs along z, but the sizes taken are those whose
+  // transform items would fit the work list
   const int rz = d3 ? rows_for(nz, mz, (long)nx * ny, kMaxGc / 2) : 1;
   if (rx < 1 || ry < 1 || rz < 1) return false;
   // columns per item of the column solve: the wide items' 16 lanes per column
@@ -244,7 +246,7 @@ Resolved resolve_opts(const bhx_opts* o) {
   R.rows_opt = o->rows;
   R.occ_opt = o->occupancy;
   R.transform = o->transform;
-  if (o->rows != 0) R.sched.rows_cap = o->rows;   // -1: fullest work items
+  if (o->rows != 0) R.sched.rows_cap = o->rows;   // -1: work items of shared launches
   if (o->occupancy > 0) R.sched.occ_r = R.sched.occ_c = o->occupancy;
   return R;
 }

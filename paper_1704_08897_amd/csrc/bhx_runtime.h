@@ -74,7 +74,7 @@ struct Layout {
 // (row and column groups of kDenseG lines).
 // rows_cap: packed rows per transform work item; 0 = the built-in policy
 // (as many as fit, reduced until the instance alone supplies kTargetItems
-// items), -1 = as many as fit.
+// items), -1 = work items of launches shared with other instances.
 bool make_layout(int nx, int ny, int nz, int prec, int mx, int my, int mz, int rows_cap,
                  Layout* L, bool dense = false);
 inline bool make_layout(int nx, int ny, int prec, int mx, int my, int rows_cap, Layout* L,
